@@ -23,12 +23,19 @@ namespace {
 // ---------------------------------------------------------------------------------
 constexpr int LN_ROWS = 8;  // rows (= wavefronts) per workgroup
 
+// Words [0, n) of p set to 0 by the launch's first workgroup (p NULL: none).
+WAM_DEV void clear_words(unsigned* p, int n) {
+  if (p == nullptr || blockIdx.x != 0) return;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
+}
+
 template <int NV>
 // (4 wavefronts per SIMD up to d = 5120: a row, 80 VGPRs, fits with the rest in 128)
 __global__ __launch_bounds__(LN_ROWS * 64, NV <= 20 ? 4 : 2) void ln_mod_kernel(const LnArgs a, int blocks_per_batch, int seg,
                                                               int seg_blocks) {
   extern __shared__ __attribute__((aligned(16))) float PQ[];  // [2][d]
   if (skip_step(a.skip)) return;
+  clear_words(a.clear, a.clear_n);
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int b = blockIdx.x / blocks_per_batch, j = blockIdx.x % blocks_per_batch;
   // a workgroup's rows lie in one segment: [0, seg) or [seg, rows_per_batch)
@@ -106,6 +113,7 @@ __global__ __launch_bounds__(LN_ROWS * 64, NC <= 10 ? 4 : 2) void ln_mod8_kernel
   // Q8: d is exactly 512 NC (no chunk of the row is conditional)
   extern __shared__ __attribute__((aligned(16))) float PQ[];  // [2][d]
   if (skip_step(a.skip)) return;
+  clear_words(a.clear, a.clear_n);
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int b = blockIdx.x / blocks_per_batch, j = blockIdx.x % blocks_per_batch;
   const bool second = j >= seg_blocks;
@@ -545,9 +553,12 @@ __global__ __launch_bounds__(256, 2) void gemv_kernel(int N, int K, int kc, cons
 
 // [cos(1000 t w_k), sin(1000 t w_k)], w_k = 10000^(-k/half); evaluated in double so the
 // large arguments (up to 1000 rad) keep full fp32 accuracy.
-__global__ void sinusoid_kernel(int B, int fd, const float* t, float* out, const int32_t* skip) {
+__global__ void sinusoid_kernel(int B, int fd, const float* t, float* out, const int32_t* skip, unsigned* clear,
+                                int clear_n) {
+  if (skip_step(skip)) return;
+  clear_words(clear, clear_n);
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * fd || skip_step(skip)) return;
+  if (i >= B * fd) return;
   const int b = i / fd, k = i % fd, half = fd / 2;
   const int kk = k < half ? k : k - half;
   const double omega = pow(10000.0, -(double)kk / (double)half);
@@ -682,8 +693,9 @@ hipError_t launch_gemv(int32_t B, int32_t N, int32_t K, const float* x, int32_t 
   return hipGetLastError();
 }
 
-hipError_t launch_sinusoid(int32_t B, int32_t fd, const float* t, float* out, hipStream_t s, const int32_t* skip) {
-  hipLaunchKernelGGL(sinusoid_kernel, dim3((B * fd + 255) / 256), dim3(256), 0, s, B, fd, t, out, skip);
+hipError_t launch_sinusoid(int32_t B, int32_t fd, const float* t, float* out, hipStream_t s, const int32_t* skip,
+                           unsigned* clear, int32_t clear_n) {
+  hipLaunchKernelGGL(sinusoid_kernel, dim3((B * fd + 255) / 256), dim3(256), 0, s, B, fd, t, out, skip, clear, clear_n);
   return hipGetLastError();
 }
 

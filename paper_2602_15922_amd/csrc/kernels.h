@@ -80,12 +80,20 @@ struct GemmArgs {
   void *rope_q, *rope_k, *rope_v;
   int32_t rope_L, rope_Dh, rope_d;
   int64_t rope_Lcap, rope_row0;
+  // scratch for products whose K is split over several workgroups (NULL: never split): fp32
+  // partial sums of part_bytes, and one counter per tile, all 0 when the launch runs (it
+  // leaves them 0)
+  float* part;
+  unsigned* count;  // GEMM_SPLIT_TILES of them
+  int64_t part_bytes;
 };
 // Internal epilogue codes beyond the public ones: the GELU output written as block-scaled
 // E4M3, (or-ed in) block-scaled FP8 A, and RoPE with the K/V append (bf16 operands).
 constexpr int WAM_EPI_GELU_MX8 = 4;
 constexpr int WAM_EPI_ROPE = 5;
 constexpr int WAM_EPI_MXA = 8;
+// counters a launch may use: its split tiles are fewer than the workgroups resident at once
+constexpr int GEMM_SPLIT_TILES = 512;
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 // n products sharing A (and, for FP8 operands, its row scales) and every size and stride,
 // each with its own W, bias, output and (FP8) column scales, in one launch; bf16 epilogue.
@@ -112,6 +120,9 @@ struct LnArgs {
   int64_t alt_off;
   // device flag of the denoising loop: while *skip > 0 every workgroup exits at entry (NULL: never)
   const int32_t* skip;
+  // words [0, clear_n) of `clear` are set to 0 (the GEMMs' split counters, before their use)
+  unsigned* clear = nullptr;
+  int32_t clear_n = 0;
   // FP8 output (q8 non-null; d a multiple of 512, at most 5120): instead of h, the E4M3
   // codes of the bf16 output rows (row stride ldq bytes) and their row scales, exactly as
   // launch_quant_rows would make them from h
@@ -173,7 +184,7 @@ hipError_t launch_gemv(int32_t B, int32_t N, int32_t K, const float* x, int32_t 
                        const void* W, const float* bias, float* out, hipStream_t s, const int32_t* skip = nullptr);
 // [B][freq_dim] sinusoid of 1000*t
 hipError_t launch_sinusoid(int32_t B, int32_t freq_dim, const float* t, float* out, hipStream_t s,
-                           const int32_t* skip = nullptr);
+                           const int32_t* skip = nullptr, unsigned* clear = nullptr, int32_t clear_n = 0);
 // latent [B][C][F][Hl][Wl] bf16 -> tokens [B][F*Hg*Wg][C*4] bf16
 hipError_t launch_patchify(int32_t B, int32_t C, int32_t F, int32_t Hl, int32_t Wl,
                            const void* z, void* tok, hipStream_t s, const int32_t* skip = nullptr);
