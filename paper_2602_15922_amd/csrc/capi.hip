@@ -782,6 +782,15 @@ wam_status embed_run(const wam_model& m, int32_t B, int32_t F, int32_t Hl, int32
                      const void* a, float* x, char* ws, hipStream_t s) {
   const wam_dims& D = m.dims;
   const int P = D.latent_ch * 4, Lv = F * (Hl / 2) * (Wl / 2), L = Lv + A;
+  if (embed_supported(D.latent_ch, A, D.act_dim)) {
+    TRY(opt_ptr(m.b_patch, "b_patch"));
+    if (A > 0) TRY(opt_ptr(m.b_ain, "b_ain"));
+    CHECK((int64_t)B * Lv * P * 2 <= INT32_MAX, WAM_EUNSUPPORTED, "the patches span 2 GiB or more");
+    EmbedArgs ea{B, D.latent_ch, F, Hl, Wl, A, D.act_dim, D.d, z, a, m.w_patch, m.w_ain, m.b_patch, m.b_ain, x};
+    LAUNCH(launch_embed(pred(ea), s));
+    return WAM_OK;
+  }
+  // wider or odd features: patches as a matrix, then the general products
   LAUNCH(launch_patchify(B, D.latent_ch, F, Hl, Wl, z, ws, s, t_skip));
   wam_gemm_desc g = gemm(B * Lv, D.d, P, WAM_EPI_F32, ws, P, m.w_patch, m.b_patch, x, D.d);
   g.out_rows = Lv; g.out_batch_stride = (int64_t)L * D.d;
@@ -812,6 +821,16 @@ wam_status head_run(const wam_model& m, int32_t B, int32_t F, int32_t Hl, int32_
                     const float* e, float* v_video, float* v_action, char* ws, hipStream_t s, int64_t e_alt = 0) {
   const wam_dims& D = m.dims;
   const int d = D.d, P = D.latent_ch * 4, Lv = F * (Hl / 2) * (Wl / 2), L = Lv + A;
+  if (head_supported(d, D.latent_ch, A, D.act_dim)) {
+    TRY(opt_ptr(m.b_hv, "b_hv"));
+    if (A > 0) TRY(opt_ptr(m.b_ha, "b_ha"));
+    CHECK(((int64_t)(B - 1) * L + Lv) * d * 2 <= INT32_MAX, WAM_EUNSUPPORTED, "the rows span 2 GiB or more");
+    HeadArgs ha{B, D.latent_ch, F, Hl, Wl, A, D.act_dim, d, D.eps, x, e, m.head_mod2, e_alt, m.w_hv, m.w_ha,
+                m.b_hv, m.b_ha, v_video, v_action};
+    LAUNCH(launch_head(pred(ha), s));
+    return WAM_OK;
+  }
+  // wider models or more outputs: the LayerNorm, the general products, the unpatchify
   const HeadWs lay = head_ws(D, B, F, Hl, Wl, A);
   char* h = ws + lay.h;
   float* tok = reinterpret_cast<float*>(ws + lay.tok);

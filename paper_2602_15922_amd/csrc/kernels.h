@@ -192,6 +192,37 @@ hipError_t launch_patchify(int32_t B, int32_t C, int32_t F, int32_t Hl, int32_t 
 hipError_t launch_unpatchify(int32_t B, int32_t C, int32_t F, int32_t Hl, int32_t Wl,
                              const float* tok, float* out, hipStream_t s, const int32_t* skip = nullptr);
 
+// Patch and action embedding into x [B][Lv + A][d] in one launch.
+struct EmbedArgs {
+  int32_t B, C, F, Hl, Wl, A, act_dim, d;
+  const void *z, *act;  // [B][C][F][Hl][Wl], [B][A][act_dim] bf16
+  const void *w_patch, *w_ain;
+  const float *b_patch, *b_ain;
+  float* x;
+  const int32_t* skip;
+};
+hipError_t launch_embed(const EmbedArgs& a, hipStream_t s);
+// whether launch_embed takes these sizes: features in whole MFMA k-steps of 16, at most 128
+inline bool embed_supported(int C, int A, int act_dim) {
+  return C % 4 == 0 && C <= 32 && (A == 0 || (act_dim % 16 == 0 && act_dim <= 128));
+}
+// The head from x [B][Lv + A][d] and e [B][d] (action rows: e + e_alt) in one launch.
+struct HeadArgs {
+  int32_t B, C, F, Hl, Wl, A, act_dim, d;
+  float eps;
+  const float *x, *e, *mod2;  // mod2 [2][d]: shift, scale
+  int64_t e_alt;
+  const void *w_hv, *w_ha;
+  const float *b_hv, *b_ha;
+  float *v_video, *v_action;
+  const int32_t* skip;
+};
+hipError_t launch_head(const HeadArgs& a, hipStream_t s);
+// whether launch_head takes these sizes: a row in the registers of a wavefront, at most 64 outputs
+inline bool head_supported(int d, int C, int A, int act_dim) {
+  return d <= 5120 && 4 * C <= 64 && (A == 0 || act_dim <= 64);
+}
+
 // Per-row E4M3 quantization of bf16 rows [M][K] (K % 8 == 0): q [M][ldq] bytes, scale [M].
 hipError_t launch_quant_rows(int32_t M, int32_t K, const void* x, int64_t ldx, void* q, int64_t ldq, float* scale,
                              hipStream_t s, const int32_t* skip = nullptr);

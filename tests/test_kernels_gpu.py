@@ -219,3 +219,42 @@ def test_embed_and_head():
                          wl.eps, C, F, Hl, Wl)
     assert rel_l2(host(vv), rv) <= 5e-3
     assert rel_l2(host(va), ra) <= 5e-3
+
+
+@pytest.mark.parametrize("d,H,C,act_dim,F,Hl,Wl,A,B", [
+    (512, 8, 16, 16, 1, 2, 2, 1, 1),        # one token of each kind
+    (1280, 10, 4, 48, 2, 6, 10, 17, 2),     # one k-step of patches, a part-filled last chunk
+    (768, 6, 32, 64, 1, 14, 18, 0, 1),      # features past 64 (general head), no actions
+    (5120, 40, 16, 16, 2, 10, 14, 33, 1),   # full rows, ragged tiles of both kinds
+    (5376, 42, 16, 16, 1, 6, 6, 5, 1),      # rows past the one-launch head
+    (512, 8, 6, 24, 1, 6, 6, 5, 1),         # features that are no whole k-steps: the general products
+])
+def test_embed_and_head_sizes(d, H, C, act_dim, F, Hl, Wl, A, B):
+    """Embedding (fp32 sums: 1e-5) and head (one bf16 intermediate: 5e-3) where the one-launch
+    kernels' tiles end and where the general path takes over; rows outside untouched."""
+    import torch
+    w = lib()
+    wl = synth.WORKLOADS["block_d512"].replace(d=d, H=H, Dh=d // H, latent_ch=C, act_dim=act_dim, F=F, Hl=Hl, Wl=Wl,
+                                               A=A, B=B)
+    log(f"embed + head d={d} C={C} act_dim={act_dim} L={wl.L}")
+    P, top, m = small_model(wl)
+    z = synth.normal(wl.seed, "z_t", (B, C, F, Hl, Wl), 1.0)
+    a = synth.normal(wl.seed, "a_t", (B, A, act_dim), 1.0)
+    f = {k: v.f64 for k, v in P.items()}
+    x = torch.full((B * wl.L + 1, d), -7.0, dtype=torch.float32, device="cuda")
+    xs = x[:-1].view(B, wl.L, d)
+    w.wam_embed_fwd(m, dev(z), dev(a), xs, workspace(w.wam_embed_workspace_bytes(m.dims, B, F, Hl, Wl)))
+    torch.cuda.synchronize()
+    assert rel_l2(host(xs), oracle.embed(z.f64, a.f64, f["w_patch"], f["b_patch"], f["w_ain"], f["b_ain"])) <= 1e-5
+    assert (host(x[-1]) == -7).all()
+    e = synth.normal(wl.seed, "e0", (B, d), 0.3, dtype="f32")
+    vv = torch.full((B * C * F * Hl * Wl + 8,), -7.0, dtype=torch.float32, device="cuda")
+    vs = vv[:-8].view(B, C, F, Hl, Wl)
+    va = torch.full((B, A, act_dim), -7.0, dtype=torch.float32, device="cuda")
+    w.wam_head_fwd(m, xs, dev(e), vs, va, workspace(w.wam_head_workspace_bytes(m.dims, B, F, Hl, Wl, A)))
+    torch.cuda.synchronize()
+    rv, ra = oracle.head(host(xs), e.f64, f["head_mod2"], wl.Lv, f["w_hv"], f["b_hv"], f["w_ha"], f["b_ha"], wl.eps,
+                         C, F, Hl, Wl)
+    assert rel_l2(host(vs), rv) <= 5e-3
+    assert A == 0 or rel_l2(host(va), ra) <= 5e-3
+    assert (host(vv[-8:]) == -7).all()
