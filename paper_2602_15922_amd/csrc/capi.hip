@@ -755,10 +755,9 @@ size_t time_ws(const wam_dims& D, int32_t B) { return align256((size_t)B * (D.fr
 wam_status time_run(const wam_model& m, int32_t B, const float* t, float* e, float* e0, char* ws, hipStream_t s,
                     unsigned* clear = nullptr) {
   const wam_dims& D = m.dims;
-  float* sinus = reinterpret_cast<float*>(ws);
-  float* hid = sinus + (size_t)B * D.freq_dim;
-  LAUNCH(launch_sinusoid(B, D.freq_dim, t, sinus, s, t_skip, clear, clear ? GEMM_SPLIT_TILES : 0));
-  LAUNCH(launch_gemv(B, D.d, D.freq_dim, sinus, GEMV_ACT_NONE, m.w_t1, m.b_t1, hid, s, t_skip));
+  float* hid = reinterpret_cast<float*>(ws);
+  LAUNCH(launch_gemv(B, D.d, D.freq_dim, t, GEMV_ACT_SINUSOID, m.w_t1, m.b_t1, hid, s, t_skip, clear,
+                     clear ? GEMM_SPLIT_TILES : 0));
   LAUNCH(launch_gemv(B, D.d, D.d, hid, GEMV_ACT_SILU, m.w_t2, m.b_t2, e, s, t_skip));
   LAUNCH(launch_gemv(B, 6 * D.d, D.d, e, GEMV_ACT_SILU, m.w_t6, m.b_t6, e0, s, t_skip));
   return WAM_OK;

@@ -5,6 +5,7 @@
 #include "kernels.h"
 
 namespace wam {
+int cu_count();
 namespace {
 
 // ---------------------------------------------------------------------------------
@@ -465,39 +466,70 @@ __global__ __launch_bounds__(256) void rope_qkv_fp8_kernel(const RopeFp8Args f) 
 }
 
 // ---------------------------------------------------------------------------------
-// Small-batch GEMV for the time MLP (B <= 8): a workgroup of 4 wavefronts owns
-// GEMV_ROWS output features, GEMV_WROWS per wavefront, for every sample b.  The input
+// Small-batch GEMV for the time MLP (B <= 8): a workgroup of 4 wavefronts owns 4 WR output
+// features, WR per wavefront, for every sample b.  The input
 // (after its activation, evaluated once per workgroup instead of once per feature) is
 // staged in LDS (all of it, or passes of up to GEMV_LDS floats); each lane then reads 8 consecutive
 // k of each of its wavefront's W rows per 16-byte load, so W streams from HBM once with
-// GEMV_WROWS loads in flight per lane.  Lane l sums k = 8 l + 512 i (+0..7), the same
-// order for any pass length (passes are multiples of 512 columns).
+// the first steps' loads in flight while the input is staged.  Lane l sums k = 8 l + 512 i (+0..7), the same
+// order for any pass length (passes are multiples of 512 columns).  WR = 4 for the wide
+// layers (fewer stagings of the input), 2 where 16 features per workgroup leave fewer than four
+// workgroups per CU.  At B = 1: 5120 x 5120 15.2 -> 12.5 us, 30720 x 5120 58.4 -> 55.0 us (5.7
+// TB/s), with the first W loads ahead of the staging instead of after it.
+// GEMV_ACT_SINUSOID: the input is the timestep embedding of t = x[b], [cos(1000 t w_k), sin(1000
+// t w_k)], w_k = 10000^(-k/half), evaluated in every workgroup's staging (in double, so the
+// large arguments, up to 1000 rad, keep full fp32 accuracy).
 // ---------------------------------------------------------------------------------
 constexpr int GEMV_MAXB = 8;
-constexpr int GEMV_WROWS = 4;
-constexpr int GEMV_ROWS = 4 * GEMV_WROWS;
+
+// A workgroup barrier that waits for LDS operations only, so that loads stay in flight.
+WAM_DEV void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4));  // lgkmcnt(0) only
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 constexpr int GEMV_LDS = 16384;
 
-template <int B>
+template <int B, int WR, bool SIN>
 __global__ __launch_bounds__(256, 2) void gemv_kernel(int N, int K, int kc, const float* __restrict__ x,
                                                    int act, const bf16* __restrict__ W,
                                                    const float* __restrict__ bias, float* __restrict__ out,
-                                                   const int32_t* skip) {
+                                                   const int32_t* skip, unsigned* clear, int clear_n) {
   extern __shared__ __attribute__((aligned(16))) float xs[];  // B * kc floats
   if (skip_step(skip)) return;
+  clear_words(clear, clear_n);
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int n0 = blockIdx.x * GEMV_ROWS + w * GEMV_WROWS;
-  float acc[B][GEMV_WROWS];
+  const int n0 = (blockIdx.x * 4 + w) * WR;
+  float acc[B][WR];
 #pragma unroll
   for (int b = 0; b < B; ++b)
 #pragma unroll
-    for (int r = 0; r < GEMV_WROWS; ++r) acc[b][r] = 0.f;
+    for (int r = 0; r < WR; ++r) acc[b][r] = 0.f;
   for (int k0 = 0; k0 < K; k0 += kc) {
     const int kn = K - k0 < kc ? K - k0 : kc;
-    __syncthreads();
-    // 4 floats per load, a thread's loads issued in groups of 8 before any is used (B * kn
-    // <= GEMV_LDS: at most GEMV_LDS / 1024 per thread; kn is a multiple of 8)
-    {
+    // the first PRE steps' W, in flight while the input is staged
+    auto load_w = [&](int kk, bf16x8 (&wv)[WR]) {
+#pragma unroll
+      for (int r = 0; r < WR; ++r)
+        wv[r] = n0 + r < N && kk < kn ? load_bf16x8(W + (int64_t)(n0 + r) * K + k0 + kk) : bf16x8{};
+    };
+    constexpr int PRE = WR == 2 && B <= 2 ? 6 : 1;
+    bf16x8 pre[PRE][WR];
+#pragma unroll
+    for (int i = 0; i < PRE; ++i) load_w(lane * 8 + 512 * i, pre[i]);
+    lds_barrier();  // every wavefront is done with the last pass's input
+    if constexpr (SIN) {
+      const int half = K / 2;
+      for (int i = threadIdx.x; i < B * kn; i += 256) {
+        const int b = i / kn, k = k0 + i - b * kn, kk = k < half ? k : k - half;
+        const double arg = 1000.0 * (double)x[b] * exp(-(double)kk / (double)half * 9.210340371976182736);  // ln 10000
+        xs[i] = (float)(k < half ? cos(arg) : sin(arg));
+      }
+    } else {
+      // 4 floats per load, a thread's loads issued in groups of 8 before any is used (B * kn
+      // <= GEMV_LDS: at most GEMV_LDS / 1024 per thread; kn is a multiple of 8)
       const int kn4 = kn >> 2, n4 = B * kn4;
 #pragma unroll
       for (int j0 = 0; j0 < GEMV_LDS / 1024; j0 += 8) {
@@ -524,46 +556,36 @@ __global__ __launch_bounds__(256, 2) void gemv_kernel(int N, int K, int kc, cons
         }
       }
     }
-    __syncthreads();
-    for (int kk = lane * 8; kk < kn; kk += 512) {
-      bf16x8 wv[GEMV_WROWS];
-#pragma unroll
-      for (int r = 0; r < GEMV_WROWS; ++r)
-        wv[r] = n0 + r < N ? load_bf16x8(W + (int64_t)(n0 + r) * K + k0 + kk) : bf16x8{};
+    lds_barrier();
+    auto add = [&](int kk, const bf16x8 (&wv)[WR]) {
 #pragma unroll
       for (int b = 0; b < B; ++b) {
-          const f32x4 x0 = *reinterpret_cast<const f32x4*>(xs + b * kn + kk);
-          const f32x4 x1 = *reinterpret_cast<const f32x4*>(xs + b * kn + kk + 4);
-          const float xv[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+        const f32x4 x0 = *reinterpret_cast<const f32x4*>(xs + b * kn + kk);
+        const f32x4 x1 = *reinterpret_cast<const f32x4*>(xs + b * kn + kk + 4);
+        const float xv[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
 #pragma unroll
-          for (int r = 0; r < GEMV_WROWS; ++r)
+        for (int r = 0; r < WR; ++r)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc[b][r] += xv[j] * (float)wv[r][j];
-        }
+          for (int j = 0; j < 8; ++j) acc[b][r] += xv[j] * (float)wv[r][j];
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < PRE; ++i)
+      if (lane * 8 + 512 * i < kn) add(lane * 8 + 512 * i, pre[i]);
+#pragma unroll(WR == 2 && B <= 2 ? 4 : 1)
+    for (int kk = lane * 8 + 512 * PRE; kk < kn; kk += 512) {
+      bf16x8 wv[WR];
+      load_w(kk, wv);
+      add(kk, wv);
     }
   }
 #pragma unroll
   for (int b = 0; b < B; ++b)
 #pragma unroll
-      for (int r = 0; r < GEMV_WROWS; ++r) {
+      for (int r = 0; r < WR; ++r) {
         const float s = wave_sum(acc[b][r]);
         if (lane == 0 && n0 + r < N) out[(int64_t)b * N + n0 + r] = s + (bias ? bias[n0 + r] : 0.f);
       }
-}
-
-// [cos(1000 t w_k), sin(1000 t w_k)], w_k = 10000^(-k/half); evaluated in double so the
-// large arguments (up to 1000 rad) keep full fp32 accuracy.
-__global__ void sinusoid_kernel(int B, int fd, const float* t, float* out, const int32_t* skip, unsigned* clear,
-                                int clear_n) {
-  if (skip_step(skip)) return;
-  clear_words(clear, clear_n);
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * fd) return;
-  const int b = i / fd, k = i % fd, half = fd / 2;
-  const int kk = k < half ? k : k - half;
-  const double omega = pow(10000.0, -(double)kk / (double)half);
-  const double arg = 1000.0 * (double)t[b] * omega;
-  out[i] = (float)(k < half ? cos(arg) : sin(arg));
 }
 
 // token (f, r, s) feature (c, ph, pw) <- z[b][c][f][2r+ph][2s+pw]
@@ -669,34 +691,40 @@ hipError_t launch_rope_qkv(const RopeArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_gemv(int32_t B, int32_t N, int32_t K, const float* x, int32_t act, const void* W,
-                       const float* bias, float* out, hipStream_t s, const int32_t* skip) {
-  if (B <= 0 || N <= 0) return hipSuccess;
-  if (B > GEMV_MAXB || K % 8 != 0) return hipErrorInvalidValue;
+namespace {
+template <int WR, bool SIN>
+hipError_t launch_gemv_rows(int32_t B, int32_t N, int32_t K, const float* x, int32_t act, const bf16* w,
+                            const float* bias, float* out, hipStream_t s, const int32_t* skip, unsigned* clear,
+                            int32_t clear_n) {
   // columns per pass: all of K when B x K floats fit, else a multiple of 512 (B <= 8: at
   // least 2048); the LDS is sized to the pass, so small inputs leave room for more
   // workgroups per CU
   const int kc = (int64_t)B * K <= GEMV_LDS ? K : (GEMV_LDS / B) & ~511;
-  const dim3 grid((N + GEMV_ROWS - 1) / GEMV_ROWS), block(256);
+  const dim3 grid((N + 4 * WR - 1) / (4 * WR)), block(256);
   const size_t lds = (size_t)B * kc * sizeof(float);
-  const bf16* w = static_cast<const bf16*>(W);
   switch (B) {
-    case 1: hipLaunchKernelGGL(gemv_kernel<1>, grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
-    case 2: hipLaunchKernelGGL(gemv_kernel<2>, grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
-    case 3: hipLaunchKernelGGL(gemv_kernel<3>, grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
-    case 4: hipLaunchKernelGGL(gemv_kernel<4>, grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
-    case 5: hipLaunchKernelGGL(gemv_kernel<5>, grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
-    case 6: hipLaunchKernelGGL(gemv_kernel<6>, grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
-    case 7: hipLaunchKernelGGL(gemv_kernel<7>, grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
-    default: hipLaunchKernelGGL(gemv_kernel<8>, grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
+    case 1: hipLaunchKernelGGL((gemv_kernel<1, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip, clear, clear_n); break;
+    case 2: hipLaunchKernelGGL((gemv_kernel<2, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip, clear, clear_n); break;
+    case 3: hipLaunchKernelGGL((gemv_kernel<3, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip, clear, clear_n); break;
+    case 4: hipLaunchKernelGGL((gemv_kernel<4, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip, clear, clear_n); break;
+    case 5: hipLaunchKernelGGL((gemv_kernel<5, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip, clear, clear_n); break;
+    case 6: hipLaunchKernelGGL((gemv_kernel<6, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip, clear, clear_n); break;
+    case 7: hipLaunchKernelGGL((gemv_kernel<7, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip, clear, clear_n); break;
+    default: hipLaunchKernelGGL((gemv_kernel<8, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip, clear, clear_n); break;
   }
   return hipGetLastError();
 }
+}  // namespace
 
-hipError_t launch_sinusoid(int32_t B, int32_t fd, const float* t, float* out, hipStream_t s, const int32_t* skip,
-                           unsigned* clear, int32_t clear_n) {
-  hipLaunchKernelGGL(sinusoid_kernel, dim3((B * fd + 255) / 256), dim3(256), 0, s, B, fd, t, out, skip, clear, clear_n);
-  return hipGetLastError();
+hipError_t launch_gemv(int32_t B, int32_t N, int32_t K, const float* x, int32_t act, const void* W,
+                       const float* bias, float* out, hipStream_t s, const int32_t* skip, unsigned* clear,
+                       int32_t clear_n) {
+  if (B <= 0 || N <= 0) return hipSuccess;
+  if (B > GEMV_MAXB || K % 8 != 0) return hipErrorInvalidValue;
+  const bf16* w = static_cast<const bf16*>(W);
+  if (act == GEMV_ACT_SINUSOID) return launch_gemv_rows<2, true>(B, N, K, x, act, w, bias, out, s, skip, clear, clear_n);
+  if (N < 64 * cu_count()) return launch_gemv_rows<2, false>(B, N, K, x, act, w, bias, out, s, skip, clear, clear_n);
+  return launch_gemv_rows<4, false>(B, N, K, x, act, w, bias, out, s, skip, clear, clear_n);
 }
 
 hipError_t launch_patchify(int32_t B, int32_t C, int32_t F, int32_t Hl, int32_t Wl, const void* z,

@@ -5,7 +5,7 @@ namespace wam {
 namespace {
 struct Bf16Tiles {
   using C64 = Cfg<64, 64, 64, 4, 2, 2, 2, 2, 1, 1>;
-  using C128 = Cfg<128, 128, 64, 4, 2, 4, 2, 2, 1, 1>;
+  using C128 = Cfg<128, 128, 64, 4, 4, 2, 2, 2, 1, 1>;
   using C192n = Cfg<192, 128, 64, 3, 2, 4, 2, 2, 2, 1>;
   using C128w = Cfg<128, 256, 64, 3, 2, 4, 2, 2, 2, 2>;
   using C192 = Cfg<192, 256, 64, 2, 2, 4, 2>;

@@ -179,12 +179,12 @@ hipError_t launch_quant_mx(int32_t rows, int32_t cols, const void* x, int64_t ld
 hipError_t launch_quant_scaled(int64_t n, const void* x, float inv, void* q, hipStream_t s);
 
 // out[b][n] = act(x[b][:]) . W[n][:] + bias[n]  (fp32 in/out, bf16 W [N][K])
-enum { GEMV_ACT_NONE = 0, GEMV_ACT_SILU = 1 };
-hipError_t launch_gemv(int32_t B, int32_t N, int32_t K, const float* x, int32_t act,
-                       const void* W, const float* bias, float* out, hipStream_t s, const int32_t* skip = nullptr);
-// [B][freq_dim] sinusoid of 1000*t
-hipError_t launch_sinusoid(int32_t B, int32_t freq_dim, const float* t, float* out, hipStream_t s,
-                           const int32_t* skip = nullptr, unsigned* clear = nullptr, int32_t clear_n = 0);
+// GEMV_ACT_SINUSOID: the input is the K-wide sinusoid of 1000 * x[b] (x [B]) instead.
+// clear, clear_n: words set to 0 by the launch (the GEMMs' split counters).
+enum { GEMV_ACT_NONE = 0, GEMV_ACT_SILU = 1, GEMV_ACT_SINUSOID = 2 };
+hipError_t launch_gemv(int32_t B, int32_t N, int32_t K, const float* x, int32_t act, const void* W,
+                       const float* bias, float* out, hipStream_t s, const int32_t* skip = nullptr,
+                       unsigned* clear = nullptr, int32_t clear_n = 0);
 // latent [B][C][F][Hl][Wl] bf16 -> tokens [B][F*Hg*Wg][C*4] bf16
 hipError_t launch_patchify(int32_t B, int32_t C, int32_t F, int32_t Hl, int32_t Wl,
                            const void* z, void* tok, hipStream_t s, const int32_t* skip = nullptr);
