@@ -513,11 +513,12 @@ wam_status mark(const BlockEvents& e, int kind, int end, hipStream_t s) {
   return WAM_OK;
 }
 
-// pq: this block's folded AdaLN shift/scale rows (AdalnFoldArgs layout, nseg segments), or
-// NULL to sum the block's and the sample's rows in each LayerNorm
+// pq: this block's folded AdaLN shift/scale rows (AdalnFoldArgs layout, nseg segments, pq_norm
+// floats from the first norm's to the second's), or NULL to sum the block's and the sample's
+// rows in each LayerNorm
 wam_status block_run(const wam_dims& D, const wam_block_weights& W, const wam_block_io& io, char* ws,
                      hipStream_t s, const BlockEvents& ev = BlockEvents{}, int32_t seg = 0, int64_t alt = 0,
-                     const float* pq = nullptr, int32_t nseg = 1) {
+                     const float* pq = nullptr, int32_t nseg = 1, int64_t pq_norm = 0) {
   const int d = D.d, B = io.B, L = io.L, M = B * L;
   const BlockWs lay = block_ws(D, B, L, io.Lc);
   void* h = ws + lay.h;
@@ -534,7 +535,7 @@ wam_status block_run(const wam_dims& D, const wam_block_weights& W, const wam_bl
 
   // 1. AdaLN: h = LN(x)(1 + scale1) + shift1
   LnArgs ln{M, L, d, D.eps, io.x, nullptr, nullptr, m6 + 0 * d, e0 + 0 * d, m6 + 1 * d, e0 + 1 * d, ms, h, seg, alt};
-  const int64_t pq_ms = (int64_t)nseg * 2 * d, pq_alt = 2 * (int64_t)d, pq_norm = (int64_t)B * pq_ms;
+  const int64_t pq_ms = (int64_t)nseg * 2 * d, pq_alt = 2 * (int64_t)d;
   if (pq) ln = LnArgs{M, L, d, D.eps, io.x, nullptr, nullptr, nullptr, pq, nullptr, pq + d, pq_ms, h, seg, pq_alt};
   // FP8 projections after the three LayerNorms: the LayerNorm writes the E4M3 rows itself
   const bool ln8 = F8 && ln_fp8_supported(d);
@@ -999,25 +1000,35 @@ BlockEvents block_events(const wam_step_io& io, int l) {
 
 // Every block's combined AdaLN rows for this step's time embeddings (e0, and at alt_e0 the
 // action rows' own), in chunks of at most ADALN_FOLD_MAX_LAYERS layers per launch.
-wam_status fold_run(const wam_model& m, int32_t B, const float* e0, int64_t alt_e0, const StepWs& lay, char* w,
-                    hipStream_t s) {
+wam_status fold_run(const wam_model& m, int32_t B, const float* e0, int64_t alt_e0, int32_t nseg, int64_t pq_layer,
+                    float* pq, hipStream_t s) {
   const wam_dims& D = m.dims;
   for (int l0 = 0; l0 < D.n_layers; l0 += ADALN_FOLD_MAX_LAYERS) {
     AdalnFoldArgs a{};
     a.n_layers = std::min(D.n_layers - l0, ADALN_FOLD_MAX_LAYERS);
-    a.d = D.d; a.B = B; a.nseg = lay.nseg;
+    a.d = D.d; a.B = B; a.nseg = nseg;
     a.e0 = e0; a.e0_stride = 6 * (int64_t)D.d; a.alt = alt_e0;
     for (int i = 0; i < a.n_layers; ++i) a.mod6[i] = m.blocks[l0 + i].mod6;
-    a.out = reinterpret_cast<float*>(w + lay.pq) + (size_t)l0 * lay.pq_layer;
-    a.layer_stride = (int64_t)lay.pq_layer;
+    a.out = pq + l0 * pq_layer;
+    a.layer_stride = pq_layer;
     a.skip = t_skip;
     LAUNCH(launch_adaln_fold(a, s));
   }
   return WAM_OK;
 }
 
-// The launch sequence of one step; arguments already validated.
-wam_status step_run(const wam_model& m, const wam_step_io& io, char* w, hipStream_t stream) {
+// What a step takes from its timesteps: the embedding rows [B][d], the modulation rows
+// [B][6][d] and every block's folded AdaLN rows (pq_layer floats per block, pq_norm from a
+// block's first norm to its second).
+struct StepTime {
+  const float *e, *e0, *pq;
+  int64_t pq_layer, pq_norm;
+};
+
+// The launch sequence of one step; arguments already validated.  given: the step's time rows
+// where the caller has them already (the denoising loop), else they are formed here from io.t.
+wam_status step_run(const wam_model& m, const wam_step_io& io, char* w, hipStream_t stream,
+                    const StepTime* given = nullptr) {
   const StepWs lay = step_ws(m, io);
   const wam_dims& D = m.dims;
   float* x = reinterpret_cast<float*>(w + lay.x);
@@ -1028,13 +1039,19 @@ wam_status step_run(const wam_model& m, const wam_step_io& io, char* w, hipStrea
   const int32_t Lv = io.F * (io.Hl / 2) * (io.Wl / 2), L = Lv + io.A;
 
   const SplitWs split = block_ws(D, io.B, L, io.Lc).split_at(w + lay.block);
-  TRY(time_run(m, io.B, io.t, e, e0, piece, stream, split.count()));
-  SplitScope scope(split);
   // DreamZero-Flash: the action rows' modulation comes from their own timestep
   const bool flash = io.t_action != nullptr && io.A > 0;
   const int64_t alt_e = flash ? (int64_t)io.B * D.d : 0, alt_e0 = flash ? (int64_t)io.B * 6 * D.d : 0;
-  if (flash) TRY(time_run(m, io.B, io.t_action, e + alt_e, e0 + alt_e0, piece, stream));
-  TRY(fold_run(m, io.B, e0, alt_e0, lay, w, stream));
+  float* pq = reinterpret_cast<float*>(w + lay.pq);
+  StepTime T{e, e0, pq, (int64_t)lay.pq_layer, (int64_t)lay.pq_layer / 2};
+  if (given) {
+    T = *given;
+  } else {
+    TRY(time_run(m, io.B, io.t, e, e0, piece, stream, split.count()));
+    if (flash) TRY(time_run(m, io.B, io.t_action, e + alt_e, e0 + alt_e0, piece, stream));
+    TRY(fold_run(m, io.B, e0, alt_e0, lay.nseg, (int64_t)lay.pq_layer, pq, stream));
+  }
+  SplitScope scope(split);
   if (!io.ctx_kv) {
     TRY(text_run(m, io.B, io.Lc, io.text, ctx, piece, stream));
     const BlockWs bl = block_ws(D, io.B, L, io.Lc);
@@ -1044,15 +1061,15 @@ wam_status step_run(const wam_model& m, const wam_step_io& io, char* w, hipStrea
   TRY(embed_run(m, io.B, io.F, io.Hl, io.Wl, io.A, io.z_t, io.a_t, x, piece, stream));
   for (int l = 0; l < D.n_layers; ++l) {
     wam_block_io b{};
-    b.x = x; b.e0 = e0; b.rope_cos = io.rope_cos; b.rope_sin = io.rope_sin;
+    b.x = x; b.e0 = T.e0; b.rope_cos = io.rope_cos; b.rope_sin = io.rope_sin;
     b.k_cache = io.k_cache[l]; b.v_cache = io.v_cache[l]; b.Lcap = io.Lcap; b.cache_len = io.cache_len;
     b.ch = io.ch; b.ctx = ctx; b.ctx_kv = io.ctx_kv ? io.ctx_kv[l] : w + lay.kv + (size_t)l * lay.kv_layer;
     b.B = io.B; b.L = L; b.Lc = io.Lc;
     b.k_exp = io.k_exp ? io.k_exp[l] : nullptr; b.v_scale = io.v_scale ? io.v_scale[l] : 1.0f;
     TRY(block_run(D, m.blocks[l], b, w + lay.block, stream, block_events(io, l), flash ? Lv : 0, alt_e0,
-                  reinterpret_cast<const float*>(w + lay.pq) + (size_t)l * lay.pq_layer, lay.nseg));
+                  T.pq + (size_t)l * T.pq_layer, lay.nseg, T.pq_norm));
   }
-  TRY(head_run(m, io.B, io.F, io.Hl, io.Wl, io.A, x, e, io.v_video, io.v_action, piece, stream, alt_e));
+  TRY(head_run(m, io.B, io.F, io.Hl, io.Wl, io.A, x, T.e, io.v_video, io.v_action, piece, stream, alt_e));
   return WAM_OK;
 }
 
@@ -1212,7 +1229,8 @@ wam_status unipc_args(const wam_flow_dims& d, float* x, float* x_last, float* co
 }
 
 struct DenoiseWs {
-  size_t step, va, vb, cos, cos_out, state, xl, ring, total;
+  size_t step, va, vb, cos, cos_out, state, xl, ring, trow, te, te0, thid, tpq, total;
+  int32_t group;  // steps whose time rows are formed together
 };
 DenoiseWs denoise_ws(const wam_model& m, const wam_step_io& io, const wam_denoise_params& p) {
   const int64_t nx = p.cfg ? 1 : io.B;
@@ -1229,6 +1247,15 @@ DenoiseWs denoise_ws(const wam_model& m, const wam_step_io& io, const wam_denois
   const bool unipc = p.solver == WAM_SOLVER_UNIPC;
   w.xl = off; off += unipc ? align256((size_t)nx * n * 4) : 0;
   w.ring = off; off += unipc ? 4 * align256((size_t)nx * n * 4) : 0;
+  // the time rows of a group of steps (one modulation segment: the loop has one schedule)
+  const size_t d = m.dims.d;
+  w.group = std::max(1, std::min(SCHED_MAX / std::max(io.B, 1), p.n_steps));
+  const size_t rows = (size_t)w.group * io.B;
+  w.trow = off; off += 256;
+  w.te = off; off += align256(rows * d * 4);
+  w.te0 = off; off += align256(rows * 6 * d * 4);
+  w.thid = off; off += time_ws(m.dims, (int32_t)rows);
+  w.tpq = off; off += align256((size_t)std::max(m.dims.n_layers, 0) * 2 * rows * 2 * d * 4);
   w.total = off;
   return w;
 }
@@ -1251,7 +1278,7 @@ wam_status update_run(const wam_model* m, const wam_step_io* io, void* ws, hipSt
   const bool flash = io->t_action != nullptr && io->A > 0;
   const int64_t alt_e0 = flash ? (int64_t)io->B * 6 * D.d : 0;
   if (flash) TRY(time_run(*m, io->B, io->t_action, e + (int64_t)io->B * D.d, e0 + alt_e0, piece, stream));
-  TRY(fold_run(*m, io->B, e0, alt_e0, lay, w, stream));
+  TRY(fold_run(*m, io->B, e0, alt_e0, lay.nseg, (int64_t)lay.pq_layer, reinterpret_cast<float*>(w + lay.pq), stream));
   // the last block only projects its K/V, so the cross K|V of the others
   if (!io->ctx_kv && D.n_layers > 1) {
     TRY(text_run(*m, io->B, io->Lc, io->text, ctx, piece, stream));
@@ -1273,7 +1300,7 @@ wam_status update_run(const wam_model* m, const wam_step_io* io, void* ws, hipSt
       TRY(block_kv_run(D, m->blocks[l], b, w + lay.block, stream, flash ? Lv : 0, alt_e0, pq, lay.nseg));
     } else {
       TRY(block_run(D, m->blocks[l], b, w + lay.block, stream, block_events(*io, l), flash ? Lv : 0, alt_e0, pq,
-                    lay.nseg));
+                    lay.nseg, (int64_t)lay.pq_layer / 2));
     }
   }
   return WAM_OK;
@@ -1715,12 +1742,35 @@ wam_status wam_denoise_chunk(const wam_model* m, const wam_step_io* io, const wa
   HIPCHECK(launch_flow_step(q, stream));
   // With caching the reuse decision lives in st on the device: a reused step's kernels
   // return at entry, the solver step applies vcur, and nothing waits for the host.
-  if (caching || p->computed) HIPCHECK(launch_loop_init(st, stream));
+  if (caching || p->computed) HIPCHECK(launch_loop_init(st, p->computed, p->n_steps, stream));
   for (int i = 0; i < p->n_steps; ++i) {
-    HIPCHECK(launch_fill(t_dev, io->B, p->t_sched[i], stream));
+    // The schedule is known beforehand, so the time embedding and the folded AdaLN rows of a group
+    // of steps are formed together (five launches per group instead of per step, the weights
+    // read once per group): rows step by step, a step's samples one after the other.
+    const wam_dims& D = m->dims;
+    const int g = i % lay.group, steps = std::min(lay.group, p->n_steps - (i - g)), rows = steps * io->B;
+    const int64_t d = D.d, pq_norm = (int64_t)rows * 2 * d;
+    float* te = reinterpret_cast<float*>(w + lay.te);
+    float* te0 = reinterpret_cast<float*>(w + lay.te0);
+    float* tpq = reinterpret_cast<float*>(w + lay.tpq);
+    if (g == 0) {
+      ScheduleArgs sa{};
+      sa.n = steps;
+      sa.B = io->B;
+      for (int k = 0; k < steps; ++k) sa.t[k] = p->t_sched[i + k];
+      sa.rows = reinterpret_cast<float*>(w + lay.trow);
+      sa.t_io = t_dev;
+      HIPCHECK(launch_schedule(sa, stream));
+      const int32_t L = io->F * (io->Hl / 2) * (io->Wl / 2) + io->A;
+      const SplitWs split = block_ws(D, io->B, L, io->Lc).split_at(w + lay.step + step_ws(*m, *io).block);
+      TRY(time_run(*m, rows, sa.rows, te, te0, w + lay.thid, stream, split.count()));
+      TRY(fold_run(*m, rows, te0, 0, 1, 2 * pq_norm, tpq, stream));
+    }
+    const StepTime T{te + (int64_t)g * io->B * d, te0 + (int64_t)g * io->B * 6 * d, tpq + (int64_t)g * io->B * 2 * d,
+                     2 * pq_norm, pq_norm};
     {
       SkipScope scope(caching ? st : nullptr);
-      TRY(step_run(*m, sio, w + lay.step, stream));
+      TRY(step_run(*m, sio, w + lay.step, stream, &T));
     }
     FlowArgs f = flow_args(fd);
     f.dt = p->t_sched[i + 1] - p->t_sched[i];
@@ -1737,7 +1787,7 @@ wam_status wam_denoise_chunk(const wam_model* m, const wam_step_io* io, const wa
       HIPCHECK(launch_flow_step(f, stream));
     }
     if (caching) HIPCHECK(launch_cosine(vcur, vprev, n, w + lay.cos, cs_dev, stream, st));
-    if (caching || p->computed)
+    if (caching)
       HIPCHECK(launch_loop_decide(st, cs_dev, p->cache_tau, p->cache_window, p->computed, i, stream));
     if (caching) HIPCHECK(launch_copy_if(st + 2, vcur, vprev, n, stream));
   }

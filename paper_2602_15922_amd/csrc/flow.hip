@@ -139,14 +139,18 @@ __global__ __launch_bounds__(256) void cos_final_kernel(const double* __restrict
   }
 }
 
-__global__ void fill_kernel(float* p, int n, float v) {
-  if ((int)threadIdx.x < n) p[threadIdx.x] = v;
+__global__ void schedule_kernel(const ScheduleArgs a) {
+  const int i = threadIdx.x / a.B, b = threadIdx.x % a.B;
+  if (i < a.n) a.rows[threadIdx.x] = a.t[i];
+  if (i == 0) a.t_io[b] = a.t[a.n - 1];
 }
 
 // DiT caching decided on the device (state layout in kernels.h), so the loop needs no
 // host round trip and can be captured in a graph.
-__global__ void loop_init_kernel(int32_t* state) {
+__global__ void loop_init_kernel(int32_t* state, int32_t* computed, int n) {
   if (threadIdx.x < 3) state[threadIdx.x] = 0;
+  if (computed)
+    for (int i = threadIdx.x; i < n; i += 64) computed[i] = 1;
 }
 
 __global__ void loop_decide_kernel(int32_t* state, const float* cs, float tau, int32_t window, int32_t* computed,
@@ -227,13 +231,14 @@ hipError_t launch_cosine(const float* x, const float* y, int64_t n, void* ws, fl
   return hipGetLastError();
 }
 
-hipError_t launch_fill(float* p, int n, float v, hipStream_t s) {
-  hipLaunchKernelGGL(fill_kernel, dim3(1), dim3(64), 0, s, p, n, v);
+hipError_t launch_schedule(const ScheduleArgs& a, hipStream_t s) {
+  if (a.n < 1 || a.n > SCHED_MAX || a.B < 1 || a.B * a.n > 64) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(schedule_kernel, dim3(1), dim3(64), 0, s, a);
   return hipGetLastError();
 }
 
-hipError_t launch_loop_init(int32_t* state, hipStream_t s) {
-  hipLaunchKernelGGL(loop_init_kernel, dim3(1), dim3(64), 0, s, state);
+hipError_t launch_loop_init(int32_t* state, int32_t* computed, int32_t n, hipStream_t s) {
+  hipLaunchKernelGGL(loop_init_kernel, dim3(1), dim3(64), 0, s, state, computed, n);
   return hipGetLastError();
 }
 

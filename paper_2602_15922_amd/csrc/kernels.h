@@ -266,16 +266,23 @@ size_t cosine_static_scratch_bytes();
 hipError_t cosine_static_scratch(void** ptr);
 hipError_t launch_cosine(const float* x, const float* y, int64_t n, void* ws, float* out, hipStream_t s,
                          const int32_t* skip = nullptr);
-// p[0..n) = v for n <= 64
-hipError_t launch_fill(float* p, int n, float v, hipStream_t s);
+// The times of at most SCHED_MAX consecutive loop steps: rows[i * B + b] = t[i] for every sample b,
+// and the step input t_io[b] = t[n - 1].
+constexpr int SCHED_MAX = 8;
+struct ScheduleArgs {
+  float t[SCHED_MAX];
+  int32_t n, B;
+  float *rows, *t_io;
+};
+hipError_t launch_schedule(const ScheduleArgs& a, hipStream_t s);
 
 // The loop's DiT-caching state on the device, three int32: [0] steps still to reuse
 // (the flag every kernel of a step reads), [1] computed steps so far, [2] 1 if the
-// latest step was computed.  init zeroes it; decide runs after step i's solver update:
+// latest step was computed.  init zeroes it and sets computed[0..n) (optional) to 1; decide runs after step i's solver update:
 // a reused step counts [0] down, a computed one (the cosine similarity cs of its velocity
 // with the previous computed one, valid when [1] >= 1) sets [0] = window when cs > tau;
 // computed[i] (optional) receives [2].  copy_if copies n floats while *flag != 0.
-hipError_t launch_loop_init(int32_t* state, hipStream_t s);
+hipError_t launch_loop_init(int32_t* state, int32_t* computed, int32_t n, hipStream_t s);
 hipError_t launch_loop_decide(int32_t* state, const float* cs, float tau, int32_t window, int32_t* computed,
                               int32_t i, hipStream_t s);
 hipError_t launch_copy_if(const int32_t* flag, const float* src, float* dst, int64_t n, hipStream_t s);
