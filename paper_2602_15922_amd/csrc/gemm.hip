@@ -3,10 +3,18 @@
 
 namespace wam {
 namespace {
+// 288x128: 4 wavefronts of 288x32, one per SIMD, each with the accumulators of nine MFMA tiles
+// (512 registers per lane): per slice it reads 10 fragments for 9 MFMAs and loads 53 KB for
+// half as many again as 192x128 tiles' products.  It pays where it makes one round of what is
+// otherwise a round and a split rest: 544 x 13824 at K = 5120, cold weights, 216 tiles 86.8 us
+// against 102 in 192x128 tiles (a library product 82.6); a block of 544 rows at d = 5120 600 ->
+// 577 us, the cache update of 1560 rows 1640 -> 1579.  Where more rounds run,
+// 128x256 tiles are faster (3152 x 5120: 150 against 169 us).
 struct Bf16Tiles {
   using C64 = Cfg<64, 64, 64, 4, 2, 2, 2, 2, 1, 1>;
   using C128 = Cfg<128, 128, 64, 4, 4, 2, 2, 2, 1, 1>;
   using C192n = Cfg<192, 128, 64, 3, 2, 4, 2, 2, 2, 1>;
+  using C288 = Cfg<288, 128, 64, 3, 1, 4, 1, 2, 4, 3>;
   using C128w = Cfg<128, 256, 64, 3, 2, 4, 2, 2, 2, 2>;
   using C192 = Cfg<192, 256, 64, 2, 2, 4, 2>;
   using C256 = Cfg<256, 256, 64, 2, 2, 4, 2>;
@@ -51,7 +59,8 @@ struct TileCost {
 };
 constexpr TileCost COST[NTILES] = {
     {64, 64, 0.25, 5.0, 1.0, 1.0, 2},   {128, 128, 0.48, 6.5, 3.0, 2.0, 1}, {192, 128, 0.73, 7.0, 5.0, 3.0, 1},
-    {128, 256, 0.85, 7.0, 6.0, 4.0, 1}, {192, 256, 1.30, 8.0, 0.0, 0.0, 1}, {256, 256, 1.42, 9.0, 0.0, 0.0, 1},
+    {288, 128, 0.95, 9.0, 0.0, 0.0, 1}, {128, 256, 0.85, 7.0, 6.0, 4.0, 1}, {192, 256, 1.30, 8.0, 0.0, 0.0, 1},
+    {256, 256, 1.42, 9.0, 0.0, 0.0, 1},
 };
 // two 64x64 workgroups on a CU share it: a slice of each takes twice as long
 constexpr double SHARED = 2.0;
@@ -70,6 +79,7 @@ GemmPlan plan_gemm(const GemmArgs& g, int ng) {
     const TileCost& c = COST[t];
     // the block-scaled output needs a wave's columns to be one 64-column block
     if (g.epi == WAM_EPI_GELU_MX8 && (t == TILE_64x64 || t == TILE_192x128)) continue;
+    if (g.fp8 && t == TILE_288x128) continue;  // bf16 only
     const long tiles = ng * up(g.M, c.bm) * up(g.N, c.bn), slots = cus * c.per_cu & ~7L;
     const double sl = c.per_cu > 1 && tiles > cus ? c.slice * SHARED : c.slice;
     GemmPlan p;

@@ -31,7 +31,7 @@ int cu_count();
 
 // The tiles a product can run in (rows x columns; gemm_tiles.h's users instantiate each for
 // their operand type), and how a launch deals them.
-enum GemmTile { TILE_64x64, TILE_128x128, TILE_192x128, TILE_128x256, TILE_192x256, TILE_256x256, NTILES };
+enum GemmTile { TILE_64x64, TILE_128x128, TILE_192x128, TILE_288x128, TILE_128x256, TILE_192x256, TILE_256x256, NTILES };
 struct GemmPlan {
   int tile = TILE_128x256;
   int whole = 0, parts = 1;  // tiles past `whole` are split over K among `parts` workgroups each
@@ -970,6 +970,7 @@ hipError_t launch_plan(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
     case TILE_64x64: if constexpr (EPI != WAM_EPI_GELU_MX8) return launch_one<typename T::C64, EPI>(g, p, s); break;
     case TILE_128x128: return launch_one<typename T::C128, EPI>(g, p, s);
     case TILE_192x128: if constexpr (EPI != WAM_EPI_GELU_MX8) return launch_one<typename T::C192n, EPI>(g, p, s); break;
+    case TILE_288x128: if constexpr (!std::is_void<typename T::C288>::value) return launch_one<typename T::C288, EPI>(g, p, s); break;
     case TILE_128x256: return launch_one<typename T::C128w, EPI>(g, p, s);
     case TILE_192x256: return launch_one<typename T::C192, EPI>(g, p, s);
     case TILE_256x256: return launch_one<typename T::C256, EPI>(g, p, s);
@@ -983,10 +984,12 @@ hipError_t launch_group_plan(const GemmArgs& g, const GemmPlan& p, const GemmGro
     case TILE_64x64: return launch_grouped<typename T::C64>(g, gg, s);
     case TILE_128x128: return launch_grouped<typename T::C128>(g, gg, s);
     case TILE_192x128: return launch_grouped<typename T::C192n>(g, gg, s);
+    case TILE_288x128: if constexpr (!std::is_void<typename T::C288>::value) return launch_grouped<typename T::C288>(g, gg, s); break;
     case TILE_128x256: return launch_grouped<typename T::C128w>(g, gg, s);
     case TILE_192x256: return launch_grouped<typename T::C192>(g, gg, s);
-    default: return launch_grouped<typename T::C256>(g, gg, s);
+    case TILE_256x256: return launch_grouped<typename T::C256>(g, gg, s);
   }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace

@@ -18,9 +18,9 @@ def lib():
 
 
 # 64x64 tiles (one row; one past a tile; a K tail below one slice, of several slices), 128x128,
-# 192x128 and 128x256 tiles with a ragged last row and column tile
+# 192x128, 288x128 and 128x256 tiles with a ragged last row and column tile
 SHAPES = [(1, 64, 64), (65, 72, 520), (63, 16, 5120), (300, 520, 40), (545, 5120, 512), (513, 10248, 520),
-          (500, 13824, 256)]
+          (500, 13824, 256), (570, 13824, 296), (289, 13832, 72), (575, 13832, 1032)]
 
 
 @pytest.mark.parametrize("M,N,K", SHAPES)
