@@ -176,6 +176,14 @@ def test_denoise_loop_plain():
     check_loop(case, [0.0, 0.3, 0.55, 0.8, 1.0])
 
 
+@pytest.mark.parametrize("B,steps", [(1, 9), (3, 3)])
+def test_denoise_loop_step_groups(B, steps):
+    """More time rows than one pass of the time MLP holds (8): a last group of one step, and
+    with three samples groups of two steps and one."""
+    case = LoopCase(small_wl(B=B, n_layers=1), 1)
+    check_loop(case, list(np.linspace(0.0, 1.0, steps + 1)))
+
+
 def test_denoise_loop_guidance_pair():
     """Classifier-free guidance over a batch of two: sample 0 conditional, sample 1
     unconditional (different text and caches), one shared state."""

@@ -177,6 +177,29 @@ def test_time_embedding():
     assert rel_l2(host(e0), re0) <= 1e-4
 
 
+@pytest.mark.parametrize("B,d", [(1, 512), (5, 512), (8, 768), (2, 2816)])
+def test_time_embedding_sizes(B, d):
+    """The time MLP's kernel over its edges: one sample, an odd count, the most (8); widths
+    whose 6 d outputs lie on both sides of the switch of the rows per workgroup (16384), and
+    K not a multiple of a pass (512).  The tolerance is the plain case's: fp32 sums of at most
+    2816 terms (2816 * 6e-8 = 1.7e-4 of the terms' magnitudes at the very worst) and the
+    sinusoid's argument, up to 1000, rounded to fp32 (6e-5)."""
+    import torch
+    w = lib()
+    wl = synth.WORKLOADS["block_d512"].replace(B=B, d=d, H=d // 64)
+    P, top, m = small_model(wl)
+    t = synth.uniform(wl.seed, "t", (B,))
+    log(f"time embedding B={B} d={d}")
+    e = torch.full((B, d), float("nan"), dtype=torch.float32, device="cuda")
+    e0 = torch.full((B, 6, d), float("nan"), dtype=torch.float32, device="cuda")
+    w.wam_time_embed_fwd(m, dev(t), e, e0, workspace(w.wam_time_embed_workspace_bytes(m.dims, B)))
+    torch.cuda.synchronize()
+    f = {k: v.f64 for k, v in P.items()}
+    re, re0 = oracle.time_embedding(t.f64, f["w_t1"], f["b_t1"], f["w_t2"], f["b_t2"], f["w_t6"], f["b_t6"])
+    assert rel_l2(host(e), re) <= 1e-4
+    assert rel_l2(host(e0), re0) <= 1e-4
+
+
 def test_text_projection():
     import torch
     w = lib()
