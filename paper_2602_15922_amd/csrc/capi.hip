@@ -32,28 +32,6 @@ const Args& pred(Args& a) {
   return a;
 }
 
-// Scratch of the call under way for the GEMMs that split K: partial sums, then the tile
-// counters, in the call's own workspace.  Set by SplitScope around the launches that follow
-// the one that clears the counters; none elsewhere, and then no GEMM splits.
-struct SplitWs {
-  char* part = nullptr;
-  size_t part_bytes = 0;
-  unsigned* count() const { return reinterpret_cast<unsigned*>(part + part_bytes); }
-};
-thread_local SplitWs t_split;
-struct SplitScope {
-  SplitWs before;
-  explicit SplitScope(const SplitWs& s) : before(t_split) { t_split = s; }
-  ~SplitScope() { t_split = before; }
-};
-const GemmArgs& pred(GemmArgs& a) {
-  a.skip = t_skip;
-  a.part = reinterpret_cast<float*>(t_split.part);
-  a.part_bytes = (int64_t)t_split.part_bytes;
-  a.count = t_split.part ? t_split.count() : nullptr;
-  return a;
-}
-
 wam_status fail(wam_status st, const char* fmt, ...) {
   char buf[512];
   va_list ap;
@@ -109,14 +87,6 @@ wam_status opt_ptr(const void* p, const char* name) {
 }
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
-
-// Bytes of split scratch for products of M rows by at most N columns: 8 parts of every 128x128
-// tile, but no more than every CU's 128x256 tile (the largest that is split) can fill.
-size_t split_part_bytes(size_t M, size_t N) {
-  const size_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
-  return std::min<size_t>(8 * tiles * 128 * 128 * 4, (size_t)256 * 128 * 256 * 4);
-}
-size_t split_bytes(size_t M, size_t N) { return align256(split_part_bytes(M, N) + GEMM_SPLIT_TILES * 4); }
 
 // Validate a chunk layout for Lq query rows and Lk key rows; on success fill the
 // per-query-chunk visible key prefix.
@@ -379,9 +349,7 @@ wam_gemm_desc gemm(int M, int N, int K, int epi, const void* A, int64_t lda, con
 // block
 // ---------------------------------------------------------------------------------
 struct BlockWs {
-  size_t h, big, q, o, ckv, q8, qs, split, total;
-  size_t part_bytes;
-  SplitWs split_at(char* ws) const { return SplitWs{ws + split, part_bytes}; }
+  size_t h, big, q, o, ckv, q8, qs, total;
 };
 // q8 / qs: an activation quantized to E4M3 for an FP8 projection and its row scales.
 BlockWs block_ws(const wam_dims& D, int32_t B, int32_t L, int32_t Lc) {
@@ -397,8 +365,6 @@ BlockWs block_ws(const wam_dims& D, int32_t B, int32_t L, int32_t Lc) {
   w.ckv = off; off += align256((size_t)B * Lc * 2 * d * 2);
   w.q8 = off; off += align256(rows * kmax);
   w.qs = off; off += align256(rows * 4);
-  w.part_bytes = split_part_bytes(rows, wide);
-  w.split = off; off += split_bytes(rows, wide);
   w.total = off;
   return w;
 }
@@ -540,13 +506,9 @@ wam_status block_run(const wam_dims& D, const wam_block_weights& W, const wam_bl
   // FP8 projections after the three LayerNorms: the LayerNorm writes the E4M3 rows itself
   const bool ln8 = F8 && ln_fp8_supported(d);
   if (ln8) ln_to_fp8(ln, q8, qs);
-  const SplitWs split = lay.split_at(ws);
-  ln.clear = split.count();
-  ln.clear_n = GEMM_SPLIT_TILES;
   TRY(mark(ev, WAM_EV_LN1, 0, s));
   LAUNCH(launch_ln_mod(pred(ln), s));
   TRY(mark(ev, WAM_EV_LN1, 1, s));
-  SplitScope scope(split);
   // 2. fused QKV projection; 3. RoPE on q, k; k, v appended to the cache rows of this chunk
   // (with an FP8 cache: q and k encoded in 32-dim blocks, q into the q buffer with its
   // exponents behind it).  With bf16 operands and cache, step 3 runs in step 2's epilogue
@@ -711,11 +673,7 @@ wam_status block_kv_run(const wam_dims& D, const wam_block_weights& W, const wam
   float* qs = reinterpret_cast<float*>(ws + lay.qs);
   const bool ln8 = F8 && ln_fp8_supported(d);
   if (ln8) ln_to_fp8(ln, q8, qs);
-  const SplitWs split = lay.split_at(ws);
-  ln.clear = split.count();
-  ln.clear_n = GEMM_SPLIT_TILES;
   LAUNCH(launch_ln_mod(pred(ln), s));
-  SplitScope scope(split);
   // rows d..3d of W_qkv (the k and v outputs) into columns d..3d of the [M][3d] buffer
   const char* wkv = F8 ? nullptr : static_cast<const char*>(W.w_qkv) + (size_t)d * d * 2;
   const float* bkv = W.b_qkv ? W.b_qkv + d : nullptr;
@@ -752,13 +710,10 @@ wam_status check_model_common(const wam_model& m) {
 
 size_t time_ws(const wam_dims& D, int32_t B) { return align256((size_t)B * (D.freq_dim + D.d) * 4); }
 
-// clear: split counters that the first launch sets to 0 (NULL: none).
-wam_status time_run(const wam_model& m, int32_t B, const float* t, float* e, float* e0, char* ws, hipStream_t s,
-                    unsigned* clear = nullptr) {
+wam_status time_run(const wam_model& m, int32_t B, const float* t, float* e, float* e0, char* ws, hipStream_t s) {
   const wam_dims& D = m.dims;
   float* hid = reinterpret_cast<float*>(ws);
-  LAUNCH(launch_gemv(B, D.d, D.freq_dim, t, GEMV_ACT_SINUSOID, m.w_t1, m.b_t1, hid, s, t_skip, clear,
-                     clear ? GEMM_SPLIT_TILES : 0));
+  LAUNCH(launch_gemv(B, D.d, D.freq_dim, t, GEMV_ACT_SINUSOID, m.w_t1, m.b_t1, hid, s, t_skip));
   LAUNCH(launch_gemv(B, D.d, D.d, hid, GEMV_ACT_SILU, m.w_t2, m.b_t2, e, s, t_skip));
   LAUNCH(launch_gemv(B, 6 * D.d, D.d, e, GEMV_ACT_SILU, m.w_t6, m.b_t6, e0, s, t_skip));
   return WAM_OK;
@@ -1038,7 +993,6 @@ wam_status step_run(const wam_model& m, const wam_step_io& io, char* w, hipStrea
   char* piece = w + lay.piece;
   const int32_t Lv = io.F * (io.Hl / 2) * (io.Wl / 2), L = Lv + io.A;
 
-  const SplitWs split = block_ws(D, io.B, L, io.Lc).split_at(w + lay.block);
   // DreamZero-Flash: the action rows' modulation comes from their own timestep
   const bool flash = io.t_action != nullptr && io.A > 0;
   const int64_t alt_e = flash ? (int64_t)io.B * D.d : 0, alt_e0 = flash ? (int64_t)io.B * 6 * D.d : 0;
@@ -1047,11 +1001,10 @@ wam_status step_run(const wam_model& m, const wam_step_io& io, char* w, hipStrea
   if (given) {
     T = *given;
   } else {
-    TRY(time_run(m, io.B, io.t, e, e0, piece, stream, split.count()));
+    TRY(time_run(m, io.B, io.t, e, e0, piece, stream));
     if (flash) TRY(time_run(m, io.B, io.t_action, e + alt_e, e0 + alt_e0, piece, stream));
     TRY(fold_run(m, io.B, e0, alt_e0, lay.nseg, (int64_t)lay.pq_layer, pq, stream));
   }
-  SplitScope scope(split);
   if (!io.ctx_kv) {
     TRY(text_run(m, io.B, io.Lc, io.text, ctx, piece, stream));
     const BlockWs bl = block_ws(D, io.B, L, io.Lc);
@@ -1272,9 +1225,7 @@ wam_status update_run(const wam_model* m, const wam_step_io* io, void* ws, hipSt
   char* piece = w + lay.piece;
   const int32_t Lv = io->F * (io->Hl / 2) * (io->Wl / 2), L = Lv + io->A;
 
-  const SplitWs split = block_ws(D, io->B, L, io->Lc).split_at(w + lay.block);
-  TRY(time_run(*m, io->B, io->t, e, e0, piece, stream, split.count()));
-  SplitScope scope(split);
+  TRY(time_run(*m, io->B, io->t, e, e0, piece, stream));
   const bool flash = io->t_action != nullptr && io->A > 0;
   const int64_t alt_e0 = flash ? (int64_t)io->B * 6 * D.d : 0;
   if (flash) TRY(time_run(*m, io->B, io->t_action, e + (int64_t)io->B * D.d, e0 + alt_e0, piece, stream));
@@ -1761,9 +1712,7 @@ wam_status wam_denoise_chunk(const wam_model* m, const wam_step_io* io, const wa
       sa.rows = reinterpret_cast<float*>(w + lay.trow);
       sa.t_io = t_dev;
       HIPCHECK(launch_schedule(sa, stream));
-      const int32_t L = io->F * (io->Hl / 2) * (io->Wl / 2) + io->A;
-      const SplitWs split = block_ws(D, io->B, L, io->Lc).split_at(w + lay.step + step_ws(*m, *io).block);
-      TRY(time_run(*m, rows, sa.rows, te, te0, w + lay.thid, stream, split.count()));
+      TRY(time_run(*m, rows, sa.rows, te, te0, w + lay.thid, stream));
       TRY(fold_run(*m, rows, te0, 0, 1, 2 * pq_norm, tpq, stream));
     }
     const StepTime T{te + (int64_t)g * io->B * d, te0 + (int64_t)g * io->B * 6 * d, tpq + (int64_t)g * io->B * 2 * d,

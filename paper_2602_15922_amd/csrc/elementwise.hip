@@ -24,19 +24,12 @@ namespace {
 // ---------------------------------------------------------------------------------
 constexpr int LN_ROWS = 8;  // rows (= wavefronts) per workgroup
 
-// Words [0, n) of p set to 0 by the launch's first workgroup (p NULL: none).
-WAM_DEV void clear_words(unsigned* p, int n) {
-  if (p == nullptr || blockIdx.x != 0) return;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
-}
-
 template <int NV>
 // (4 wavefronts per SIMD up to d = 5120: a row, 80 VGPRs, fits with the rest in 128)
 __global__ __launch_bounds__(LN_ROWS * 64, NV <= 20 ? 4 : 2) void ln_mod_kernel(const LnArgs a, int blocks_per_batch, int seg,
                                                               int seg_blocks) {
   extern __shared__ __attribute__((aligned(16))) float PQ[];  // [2][d]
   if (skip_step(a.skip)) return;
-  clear_words(a.clear, a.clear_n);
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int b = blockIdx.x / blocks_per_batch, j = blockIdx.x % blocks_per_batch;
   // a workgroup's rows lie in one segment: [0, seg) or [seg, rows_per_batch)
@@ -114,7 +107,6 @@ __global__ __launch_bounds__(LN_ROWS * 64, NC <= 10 ? 4 : 2) void ln_mod8_kernel
   // Q8: d is exactly 512 NC (no chunk of the row is conditional)
   extern __shared__ __attribute__((aligned(16))) float PQ[];  // [2][d]
   if (skip_step(a.skip)) return;
-  clear_words(a.clear, a.clear_n);
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int b = blockIdx.x / blocks_per_batch, j = blockIdx.x % blocks_per_batch;
   const bool second = j >= seg_blocks;
@@ -496,10 +488,9 @@ template <int B, int WR, bool SIN>
 __global__ __launch_bounds__(256, 2) void gemv_kernel(int N, int K, int kc, const float* __restrict__ x,
                                                    int act, const bf16* __restrict__ W,
                                                    const float* __restrict__ bias, float* __restrict__ out,
-                                                   const int32_t* skip, unsigned* clear, int clear_n) {
+                                                   const int32_t* skip) {
   extern __shared__ __attribute__((aligned(16))) float xs[];  // B * kc floats
   if (skip_step(skip)) return;
-  clear_words(clear, clear_n);
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int n0 = (blockIdx.x * 4 + w) * WR;
   float acc[B][WR];
@@ -694,8 +685,7 @@ hipError_t launch_rope_qkv(const RopeArgs& a, hipStream_t s) {
 namespace {
 template <int WR, bool SIN>
 hipError_t launch_gemv_rows(int32_t B, int32_t N, int32_t K, const float* x, int32_t act, const bf16* w,
-                            const float* bias, float* out, hipStream_t s, const int32_t* skip, unsigned* clear,
-                            int32_t clear_n) {
+                            const float* bias, float* out, hipStream_t s, const int32_t* skip) {
   // columns per pass: all of K when B x K floats fit, else a multiple of 512 (B <= 8: at
   // least 2048); the LDS is sized to the pass, so small inputs leave room for more
   // workgroups per CU
@@ -703,28 +693,27 @@ hipError_t launch_gemv_rows(int32_t B, int32_t N, int32_t K, const float* x, int
   const dim3 grid((N + 4 * WR - 1) / (4 * WR)), block(256);
   const size_t lds = (size_t)B * kc * sizeof(float);
   switch (B) {
-    case 1: hipLaunchKernelGGL((gemv_kernel<1, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip, clear, clear_n); break;
-    case 2: hipLaunchKernelGGL((gemv_kernel<2, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip, clear, clear_n); break;
-    case 3: hipLaunchKernelGGL((gemv_kernel<3, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip, clear, clear_n); break;
-    case 4: hipLaunchKernelGGL((gemv_kernel<4, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip, clear, clear_n); break;
-    case 5: hipLaunchKernelGGL((gemv_kernel<5, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip, clear, clear_n); break;
-    case 6: hipLaunchKernelGGL((gemv_kernel<6, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip, clear, clear_n); break;
-    case 7: hipLaunchKernelGGL((gemv_kernel<7, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip, clear, clear_n); break;
-    default: hipLaunchKernelGGL((gemv_kernel<8, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip, clear, clear_n); break;
+    case 1: hipLaunchKernelGGL((gemv_kernel<1, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
+    case 2: hipLaunchKernelGGL((gemv_kernel<2, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
+    case 3: hipLaunchKernelGGL((gemv_kernel<3, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
+    case 4: hipLaunchKernelGGL((gemv_kernel<4, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
+    case 5: hipLaunchKernelGGL((gemv_kernel<5, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
+    case 6: hipLaunchKernelGGL((gemv_kernel<6, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
+    case 7: hipLaunchKernelGGL((gemv_kernel<7, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
+    default: hipLaunchKernelGGL((gemv_kernel<8, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
   }
   return hipGetLastError();
 }
 }  // namespace
 
 hipError_t launch_gemv(int32_t B, int32_t N, int32_t K, const float* x, int32_t act, const void* W,
-                       const float* bias, float* out, hipStream_t s, const int32_t* skip, unsigned* clear,
-                       int32_t clear_n) {
+                       const float* bias, float* out, hipStream_t s, const int32_t* skip) {
   if (B <= 0 || N <= 0) return hipSuccess;
   if (B > GEMV_MAXB || K % 8 != 0) return hipErrorInvalidValue;
   const bf16* w = static_cast<const bf16*>(W);
-  if (act == GEMV_ACT_SINUSOID) return launch_gemv_rows<2, true>(B, N, K, x, act, w, bias, out, s, skip, clear, clear_n);
-  if (N < 64 * cu_count()) return launch_gemv_rows<2, false>(B, N, K, x, act, w, bias, out, s, skip, clear, clear_n);
-  return launch_gemv_rows<4, false>(B, N, K, x, act, w, bias, out, s, skip, clear, clear_n);
+  if (act == GEMV_ACT_SINUSOID) return launch_gemv_rows<2, true>(B, N, K, x, act, w, bias, out, s, skip);
+  if (N < 64 * cu_count()) return launch_gemv_rows<2, false>(B, N, K, x, act, w, bias, out, s, skip);
+  return launch_gemv_rows<4, false>(B, N, K, x, act, w, bias, out, s, skip);
 }
 
 hipError_t launch_patchify(int32_t B, int32_t C, int32_t F, int32_t Hl, int32_t Wl, const void* z,

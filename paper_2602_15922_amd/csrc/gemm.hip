@@ -6,7 +6,7 @@ namespace {
 // 288x128: 4 wavefronts of 288x32, one per SIMD, each with the accumulators of nine MFMA tiles
 // (512 registers per lane): per slice it reads 10 fragments for 9 MFMAs and loads 53 KB for
 // half as many again as 192x128 tiles' products.  It pays where it makes one round of what is
-// otherwise a round and a split rest: 544 x 13824 at K = 5120, cold weights, 216 tiles 86.8 us
+// otherwise one and a part: 544 x 13824 at K = 5120, cold weights, 216 tiles 86.8 us
 // against 102 in 192x128 tiles (a library product 82.6); a block of 544 rows at d = 5120 600 ->
 // 577 us, the cache update of 1560 rows 1640 -> 1579.  Where more rounds run,
 // 128x256 tiles are faster (3152 x 5120: 150 against 169 us).
@@ -49,30 +49,28 @@ namespace {
 // What a tile costs (us), from launches with cold weights (each its own W, as in a model's
 // step) over M = 32 ... 3152, N = 16 ... 15360, K = 512 ... 13824: `slice` per 128-byte slice
 // of K for a workgroup alone on its CU, `fixed` for the launch, the prologue and the
-// epilogue, `part` for writing and adding up the partial sums of a tile split in two, `more`
-// for every further part.  FP8 and bf16 slices cost about the same: both are held by the
-// loads into LDS (64 bytes per cycle and CU) and their latency.
+// epilogue.  FP8 and bf16 slices cost about the same: both are held by the loads into LDS
+// (64 bytes per cycle and CU) and their latency.
 struct TileCost {
   int bm, bn;
-  double slice, fixed, part, more;
+  double slice, fixed;
   int per_cu;
 };
 constexpr TileCost COST[NTILES] = {
-    {64, 64, 0.25, 5.0, 1.0, 1.0, 2},   {128, 128, 0.48, 6.5, 3.0, 2.0, 1}, {192, 128, 0.73, 7.0, 5.0, 3.0, 1},
-    {288, 128, 0.95, 9.0, 0.0, 0.0, 1}, {128, 256, 0.85, 7.0, 6.0, 4.0, 1}, {192, 256, 1.30, 8.0, 0.0, 0.0, 1},
-    {256, 256, 1.42, 9.0, 0.0, 0.0, 1},
+    {64, 64, 0.25, 5.0, 2},   {128, 128, 0.48, 6.5, 1}, {192, 128, 0.73, 7.0, 1}, {288, 128, 0.95, 9.0, 1},
+    {128, 256, 0.85, 7.0, 1}, {192, 256, 1.30, 8.0, 1}, {256, 256, 1.42, 9.0, 1},
 };
 // two 64x64 workgroups on a CU share it: a slice of each takes twice as long
 constexpr double SHARED = 2.0;
-constexpr int MAX_PARTS = 8;
 
 GemmPlan plan_gemm(const GemmArgs& g, int ng) {
   const long cus = cu_count();
   const int slices = (g.K * (g.fp8 ? 1 : 2) + 127) / 128;
   auto up = [](long a, long b) { return (a + b - 1) / b; };
-  // Every tile over all columns.  A launch costs its rounds of resident workgroups; where
-  // scratch is given, the tiles past the last whole round are split over K so that their
-  // parts fill the chip (at least 4 slices each).
+  // Every tile over all columns: a launch costs its rounds of resident workgroups.  K is never
+  // split, whatever a tile leaves idle: every tile sums an output's products in the same order
+  // (ascending K, one MFMA chain), so a row's bits depend neither on the tile nor on how many
+  // rows the call has.
   GemmPlan best;
   double least = 0.0;
   for (int t = 0; t < NTILES; ++t) {
@@ -84,22 +82,7 @@ GemmPlan plan_gemm(const GemmArgs& g, int ng) {
     const double sl = c.per_cu > 1 && tiles > cus ? c.slice * SHARED : c.slice;
     GemmPlan p;
     p.tile = t;
-    double cost = up(tiles, slots) * (slices * sl + c.fixed);
-    if (c.bm * c.bn <= 128 * 256 && ng == 1) {
-      const long whole = tiles / slots * slots, rest = tiles - whole;
-      const int most = slices / 4 < MAX_PARTS ? slices / 4 : MAX_PARTS;
-      for (int parts = 2; parts <= most && rest * parts <= slots; ++parts) {
-        if (!g.part || rest * parts * c.bm * c.bn * 4 > g.part_bytes) break;
-        const double sp = c.per_cu > 1 && (whole > 0 || rest * parts > cus) ? c.slice * SHARED : c.slice;
-        const double with = whole / slots * (slices * sl + c.fixed) + up(slices, parts) * sp + c.fixed + c.part +
-                            c.more * (parts - 2);
-        if (rest > 0 && with < cost) {
-          cost = with;
-          p.whole = (int)whole;
-          p.parts = parts;
-        }
-      }
-    }
+    const double cost = up(tiles, slots) * (slices * sl + c.fixed);
     if (t == 0 || least == 0.0 || cost < least) {
       least = cost;
       best = p;

@@ -1,9 +1,7 @@
 // The FP8 (E4M3) tiles of the GEMM: slices of 128 bytes per row, as the bf16 tiles' slices,
 // so the same tile shapes and rings; half the matrix-core time per byte.  Measured at K = 5120
 // (40 slices) with cold weights, M x N: 544 x 5120 38.8 us in 128x128 tiles of 4 wavefronts
-// and 2 stages, 26.3 in 8 wavefronts and 4 stages; 544 x 13824 65.1 us in 192x256 tiles,
-// 62.0 in 192x128 ones with the last round split over K; 544 x 5120 at K = 13824 84.1 us in
-// 128x256 tiles, 51.1 in 192x128 ones split in two.
+// and 2 stages, 26.3 in 8 wavefronts and 4 stages.
 #include "gemm_tiles.h"
 
 namespace wam {

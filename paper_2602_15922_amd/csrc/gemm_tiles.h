@@ -34,8 +34,7 @@ int cu_count();
 enum GemmTile { TILE_64x64, TILE_128x128, TILE_192x128, TILE_288x128, TILE_128x256, TILE_192x256, TILE_256x256, NTILES };
 struct GemmPlan {
   int tile = TILE_128x256;
-  int whole = 0, parts = 1;  // tiles past `whole` are split over K among `parts` workgroups each
-  int two = -1, c1 = 0;      // two column ranges: c1 columns of `tile`, the rest in tile `two`
+  int two = -1, c1 = 0;  // two column ranges: c1 columns of `tile`, the rest in tile `two`
 };
 hipError_t launch_gemm_fp8(const GemmArgs& g, const GemmPlan& p, const GemmGroup* gg, hipStream_t s);
 namespace {
@@ -61,7 +60,6 @@ struct Cfg {
   static constexpr int NIB = BN * CPR / (NW * 64);  // (W)
   static constexpr int STAGE = (BM + BN) * ROWB;  // bytes per stage
   static constexpr bool MXA = false;              // block-scaled FP8 A (MxA below)
-  static constexpr bool SPLITS = BM * BN <= 128 * 256;  // built to split tiles over K
   static constexpr int NL = NIA + NIB;            // tile loads per slice per wave
   static constexpr int NI = NL;                   // vector memory instructions per slice per wave
   // Loads of slice t + STAGES issued in the last k-step of slice t, whose barrier frees their
@@ -458,11 +456,8 @@ WAM_DEV char* lds_ring() {
 // the operand ring and the epilogue's staging in the first STAGES * STAGE of LBYTES
 // bytes of LDS.
 // EPI: the epilogue (low 3 bits), or-ed with WAM_EPI_MXA for block-scaled FP8 A.
-// SPLIT: the tile's K slices are dealt to `parts` workgroups, this one taking part `part`
-// of split tile number `tile`; the workgroup that finishes last adds the parts' accumulators,
-// in the order of the parts whoever is last, and runs the epilogue.
-template <typename C0, int EPI, int LBYTES = C0::STAGES * C0::STAGE, bool SPLIT = false>
-WAM_DEV void gemm_tile(const GemmArgs g, int tm, int tn, int col0, int tile = 0, int part = 0, int parts = 1) {
+template <typename C0, int EPI, int LBYTES = C0::STAGES * C0::STAGE>
+WAM_DEV void gemm_tile(const GemmArgs g, int tm, int tn, int col0) {
   using C = typename std::conditional<(EPI & WAM_EPI_MXA) != 0, MxA<C0>, C0>::type;
   constexpr int E = EPI & 7;
   static_assert(!C::MXA || C::EB == 1, "block-scaled A is FP8");
@@ -478,17 +473,9 @@ WAM_DEV void gemm_tile(const GemmArgs g, int tm, int tn, int col0, int tile = 0,
   const int hh = lane >> 5, l32 = lane & 31;
   const int wm = w / C::WN, wn = w % C::WN;
 
-  // this workgroup's slices: all of K, or part `part` of it
-  int K = g.K, kt0 = 0;
-  if constexpr (SPLIT) {
-    const int all = (g.K + BK - 1) / BK;
-    kt0 = all * part / parts;
-    const int kt1 = all * (part + 1) / parts;
-    K = (kt1 * BK < g.K ? kt1 * BK : g.K) - kt0 * BK;
-  }
   GemmLane<C> L;
-  L.A = static_cast<const char*>(g.A) + (int64_t)kt0 * BK * C::EB;
-  L.W = static_cast<const char*>(g.W) + (int64_t)kt0 * BK * C::EB;
+  L.A = g.A;
+  L.W = g.W;
   L.w = w;
   // Load units: unit u of a slice is row u/CPR, physical chunk u%CPR, which holds
   // logical chunk pch(row, u%CPR) (the XOR is an involution).
@@ -511,7 +498,7 @@ WAM_DEV void gemm_tile(const GemmArgs g, int tm, int tn, int col0, int tile = 0,
     L.b_off[c] = (int)(C::EB * ((int64_t)r * g.ldw + L.klb[c]));
   }
   if constexpr (C::MXA) {  // the exponents of the lane's A rows (clamped to the last row)
-    L.ae = g.a_exp + kt0 * g.a_lde;
+    L.ae = g.a_exp;
     L.ae_ld = g.a_lde;
 #pragma unroll
     for (int a = 0; a < C::TM; ++a) {
@@ -536,7 +523,7 @@ WAM_DEV void gemm_tile(const GemmArgs g, int tm, int tn, int col0, int tile = 0,
 #pragma unroll
     for (int b = 0; b < C::TN; ++b) acc[a][b] = f32x16{};
 
-  const int nk = (K + BK - 1) / BK;
+  const int nk = (g.K + BK - 1) / BK;
   constexpr int NI = C::NI;  // loads per slice per wave
   static_assert(C::KS % 2 == 0, "fragment slots alternate per k-step and slice");
   unsigned ering[S][C::TM];  // block-scaled A: exponents of the slice in each stage
@@ -550,8 +537,8 @@ WAM_DEV void gemm_tile(const GemmArgs g, int tm, int tn, int col0, int tile = 0,
 #pragma unroll
     for (int p = 0; p < S; ++p) {
       const int kp = p < nk ? p : nk - 1;
-      if (p < S - 1) fetch_slice<C, true>(smem, p, L, kp, K);
-      else fetch_slice<C, true, 0, C::NFIRST>(smem, p, L, kp, K);
+      if (p < S - 1) fetch_slice<C, true>(smem, p, L, kp, g.K);
+      else fetch_slice<C, true, 0, C::NFIRST>(smem, p, L, kp, g.K);
       fetch_exp<C>(L, kp, ering[p]);
     }
     WAM_WAIT_VMCNT((S - 1) * NI - (C::NL - C::NFIRST));
@@ -560,13 +547,13 @@ WAM_DEV void gemm_tile(const GemmArgs g, int tm, int tn, int col0, int tile = 0,
 #pragma unroll
     for (int p = 0; p < S; ++p)
       if (p < nk) {
-        if (p < S - 1) fetch_slice<C>(smem, p, L, p, K);
-        else fetch_slice<C, false, 0, C::NFIRST>(smem, p, L, p, K);
+        if (p < S - 1) fetch_slice<C>(smem, p, L, p, g.K);
+        else fetch_slice<C, false, 0, C::NFIRST>(smem, p, L, p, g.K);
       }
     if (nk >= S) WAM_WAIT_VMCNT((S - 1) * NI - (C::NL - C::NFIRST));
     else wait_slices<NI, S - 2>(nk - 1);
-    if (BK > K) {
-      zero_tail<C>(smem, 0, L, 0, K, lane);
+    if (BK > g.K) {
+      zero_tail<C>(smem, 0, L, 0, g.K, lane);
       WAM_WAIT_LGKMCNT0();
     }
     block_barrier();
@@ -578,74 +565,14 @@ WAM_DEV void gemm_tile(const GemmArgs g, int tm, int tn, int col0, int tile = 0,
   // here has a successor, prefetches a slice < nk, and waits for a full slice
   if constexpr (C::MXA) {
     // K is a multiple of the slice: S slices per iteration, then the last nk % S
-    for (; kt + S <= nk; kt += S) steady_group<C, 0>(smem, L, kt, K, acc, fa, fb, ering, nk);
-    steady_rest<C, 0>(smem, L, kt, K, acc, fa, fb, ering, nk);
+    for (; kt + S <= nk; kt += S) steady_group<C, 0>(smem, L, kt, g.K, acc, fa, fb, ering, nk);
+    steady_rest<C, 0>(smem, L, kt, g.K, acc, fa, fb, ering, nk);
   } else {
-    for (; kt + 2 * S + 1 <= nk && (kt + 2 * S + 1) * BK <= K; kt += S)
-      steady_group<C, 0>(smem, L, kt, K, acc, fa, fb, ering);
-    for (; kt < nk; ++kt) slice_tail<C>(smem, L, kt, nk, K, lane, acc, fa, fb, ering);
+    for (; kt + 2 * S + 1 <= nk && (kt + 2 * S + 1) * BK <= g.K; kt += S)
+      steady_group<C, 0>(smem, L, kt, g.K, acc, fa, fb, ering);
+    for (; kt < nk; ++kt) slice_tail<C>(smem, L, kt, nk, g.K, lane, acc, fa, fb, ering);
   }
   __syncthreads();  // all waves done with the operand ring before it is reused
-  if constexpr (SPLIT) {
-    // Partial sums in the accumulators' own layout (8 bytes per lane, whole wavefronts
-    // contiguous), then one count per tile.  The parts of a tile may run on different XCDs,
-    // whose L2s are not coherent for ordinary stores, so the partials are written and read
-    // with device-scope relaxed atomics: they go through to memory and past the L2, and the
-    // wait before the count makes them visible to whoever sees it.  (A device-scope fence
-    // instead writes back the XCD's whole L2 per wavefront: 5-10 us per launch.)  The
-    // counter wraps back to 0 at the last arrival, so a call leaves it as it found it.
-    if (parts > 1) {
-      constexpr int NV = C::TM * C::TN * 8, PART = C::NT * NV;  // 8-byte units per lane, per part
-      uint64_t* pt = reinterpret_cast<uint64_t*>(g.part) + (int64_t)tile * parts * PART + tid;
-      uint64_t* mine = pt + (int64_t)part * PART;
-#pragma unroll
-      for (int a = 0; a < C::TM; ++a)
-#pragma unroll
-        for (int b = 0; b < C::TN; ++b)
-#pragma unroll
-          for (int r = 0; r < 8; ++r)
-            __hip_atomic_store(mine + ((a * C::TN + b) * 8 + r) * C::NT,
-                               (uint64_t)__float_as_uint(acc[a][b][2 * r]) |
-                                   (uint64_t)__float_as_uint(acc[a][b][2 * r + 1]) << 32,
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      WAM_WAIT_VMCNT(0);
-      __syncthreads();
-      unsigned* const seen = reinterpret_cast<unsigned*>(smem);
-      if (tid == 0) *seen = atomicInc(g.count + tile, (unsigned)(parts - 1));
-      __syncthreads();
-      const bool last = *seen == (unsigned)(parts - 1);
-      __syncthreads();  // the word is read before the ring is reused
-      if (!last) return;
-      // the sum of the parts in their order: with two, own + other is the same number
-      // whichever is last; with more, from memory
-      if (parts > 2) {
-#pragma unroll
-        for (int a = 0; a < C::TM; ++a)
-#pragma unroll
-          for (int b = 0; b < C::TN; ++b) acc[a][b] = f32x16{};
-      }
-#pragma unroll 1
-      for (int p = 0; p < parts; ++p) {
-        if (parts == 2 && p == part) continue;
-        const uint64_t* src = pt + (int64_t)p * PART;
-#pragma unroll
-        for (int a = 0; a < C::TM; ++a)
-#pragma unroll
-          for (int b = 0; b < C::TN; ++b) {
-            uint64_t v[8];
-#pragma unroll
-            for (int r = 0; r < 8; ++r)
-              v[r] = __hip_atomic_load(src + ((a * C::TN + b) * 8 + r) * C::NT, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-              acc[a][b][2 * r] += __uint_as_float((unsigned)v[r]);
-              acc[a][b][2 * r + 1] += __uint_as_float((unsigned)(v[r] >> 32));
-            }
-          }
-      }
-    }
-  }
 
   // ---- epilogue: each wave stages 32 rows x WCOLS of its tile through LDS (reusing
   // the operand buffers) so every lane then owns 4 consecutive columns of one row and
@@ -826,41 +753,10 @@ WAM_DEV void grouped_tile(int slot, int tiles_m, int tiles_n, int& tm, int& tn) 
 template <typename C, int EPI>
 __global__ __launch_bounds__(C::NT, C::OCC) void gemm_nt(const GemmArgs g, int tiles_m, int tiles_n) {
   if (skip_step(g.skip)) return;
-  const int total = tiles_m * tiles_n;
-  constexpr int GM = 8;
-  for (int slot = blockIdx.x; slot < total; slot += gridDim.x) {
-    const int lid = xcd_tile(slot, total);
-    const int per = GM * tiles_n, grp = lid / per, first = grp * GM;
-    const int gm = tiles_m - first < GM ? tiles_m - first : GM;
-    const int r = lid - grp * per;
-    gemm_tile<C, EPI>(g, first + r % gm, r / gm, 0);
-  }
-}
-
-// The same with the tiles past the last whole round of workgroups (all of them, where there
-// is no whole round) split over K: tiles [0, whole) as above, each of the rest dealt to
-// `parts` workgroups (gemm_tile's SPLIT), the parts of a tile neighbours in dispatch order
-// so that they run at the same time.
-template <typename C, int EPI>
-__global__ __launch_bounds__(C::NT, C::OCC) void gemm_nt_split(const GemmArgs g, int tiles_m, int tiles_n, int whole,
-                                                               int parts) {
-  if (skip_step(g.skip)) return;
-  const int rest = (tiles_m * tiles_n - whole) * parts;
-  for (int slot = blockIdx.x; slot < whole + rest; slot += gridDim.x) {
-    int t, part = 0, np = 1;
-    if (slot < whole) {
-      t = xcd_tile(slot, whole);
-    } else {  // slot - whole keeps a workgroup's slots on one XCD range (whole: a multiple of 8)
-      const int lid = xcd_tile(slot - whole, rest);
-      t = whole + lid / parts;
-      part = lid % parts;
-      np = parts;
-    }
-    constexpr int GM = 8;
-    const int per = GM * tiles_n, grp = t / per, first = grp * GM;
-    const int gm = tiles_m - first < GM ? tiles_m - first : GM;
-    const int r = t - grp * per;
-    gemm_tile<C, EPI, C::STAGES * C::STAGE, true>(g, first + r % gm, r / gm, 0, t - whole, part, np);
+  for (int slot = blockIdx.x; slot < tiles_m * tiles_n; slot += gridDim.x) {
+    int tm, tn;
+    grouped_tile(slot, tiles_m, tiles_n, tm, tn);
+    gemm_tile<C, EPI>(g, tm, tn, 0);
   }
 }
 
@@ -926,15 +822,9 @@ int persistent_grid(long slots) {
 }
 
 template <typename Cf, int EPI>
-hipError_t launch_one(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
+hipError_t launch_one(const GemmArgs& g, hipStream_t s) {
   const int tm = (g.M + Cf::BM - 1) / Cf::BM, tn = (g.N + Cf::BN - 1) / Cf::BN;
-  if constexpr (Cf::SPLITS) {
-    const long rest = ((long)tm * tn - p.whole) * p.parts;
-    hipLaunchKernelGGL((gemm_nt_split<Cf, EPI>), dim3(persistent_grid<Cf>(p.whole + rest)), dim3(Cf::NT), 0, s, g, tm,
-                       tn, p.whole, p.parts);
-  } else {
-    hipLaunchKernelGGL((gemm_nt<Cf, EPI>), dim3(persistent_grid<Cf>((long)tm * tn)), dim3(Cf::NT), 0, s, g, tm, tn);
-  }
+  hipLaunchKernelGGL((gemm_nt<Cf, EPI>), dim3(persistent_grid<Cf>((long)tm * tn)), dim3(Cf::NT), 0, s, g, tm, tn);
   return hipGetLastError();
 }
 
@@ -967,13 +857,13 @@ hipError_t launch_plan(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
   }
   switch (p.tile) {
     // the block-scaled output needs a wave's columns to be one 64-column block
-    case TILE_64x64: if constexpr (EPI != WAM_EPI_GELU_MX8) return launch_one<typename T::C64, EPI>(g, p, s); break;
-    case TILE_128x128: return launch_one<typename T::C128, EPI>(g, p, s);
-    case TILE_192x128: if constexpr (EPI != WAM_EPI_GELU_MX8) return launch_one<typename T::C192n, EPI>(g, p, s); break;
-    case TILE_288x128: if constexpr (!std::is_void<typename T::C288>::value) return launch_one<typename T::C288, EPI>(g, p, s); break;
-    case TILE_128x256: return launch_one<typename T::C128w, EPI>(g, p, s);
-    case TILE_192x256: return launch_one<typename T::C192, EPI>(g, p, s);
-    case TILE_256x256: return launch_one<typename T::C256, EPI>(g, p, s);
+    case TILE_64x64: if constexpr (EPI != WAM_EPI_GELU_MX8) return launch_one<typename T::C64, EPI>(g, s); break;
+    case TILE_128x128: return launch_one<typename T::C128, EPI>(g, s);
+    case TILE_192x128: if constexpr (EPI != WAM_EPI_GELU_MX8) return launch_one<typename T::C192n, EPI>(g, s); break;
+    case TILE_288x128: if constexpr (!std::is_void<typename T::C288>::value) return launch_one<typename T::C288, EPI>(g, s); break;
+    case TILE_128x256: return launch_one<typename T::C128w, EPI>(g, s);
+    case TILE_192x256: return launch_one<typename T::C192, EPI>(g, s);
+    case TILE_256x256: return launch_one<typename T::C256, EPI>(g, s);
   }
   return hipErrorInvalidValue;
 }

@@ -80,20 +80,12 @@ struct GemmArgs {
   void *rope_q, *rope_k, *rope_v;
   int32_t rope_L, rope_Dh, rope_d;
   int64_t rope_Lcap, rope_row0;
-  // scratch for products whose K is split over several workgroups (NULL: never split): fp32
-  // partial sums of part_bytes, and one counter per tile, all 0 when the launch runs (it
-  // leaves them 0)
-  float* part;
-  unsigned* count;  // GEMM_SPLIT_TILES of them
-  int64_t part_bytes;
 };
 // Internal epilogue codes beyond the public ones: the GELU output written as block-scaled
 // E4M3, (or-ed in) block-scaled FP8 A, and RoPE with the K/V append (bf16 operands).
 constexpr int WAM_EPI_GELU_MX8 = 4;
 constexpr int WAM_EPI_ROPE = 5;
 constexpr int WAM_EPI_MXA = 8;
-// counters a launch may use: its split tiles are fewer than the workgroups resident at once
-constexpr int GEMM_SPLIT_TILES = 512;
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 // n products sharing A (and, for FP8 operands, its row scales) and every size and stride,
 // each with its own W, bias, output and (FP8) column scales, in one launch; bf16 epilogue.
@@ -120,9 +112,6 @@ struct LnArgs {
   int64_t alt_off;
   // device flag of the denoising loop: while *skip > 0 every workgroup exits at entry (NULL: never)
   const int32_t* skip;
-  // words [0, clear_n) of `clear` are set to 0 (the GEMMs' split counters, before their use)
-  unsigned* clear = nullptr;
-  int32_t clear_n = 0;
   // FP8 output (q8 non-null; d a multiple of 512, at most 5120): instead of h, the E4M3
   // codes of the bf16 output rows (row stride ldq bytes) and their row scales, exactly as
   // launch_quant_rows would make them from h
@@ -180,11 +169,9 @@ hipError_t launch_quant_scaled(int64_t n, const void* x, float inv, void* q, hip
 
 // out[b][n] = act(x[b][:]) . W[n][:] + bias[n]  (fp32 in/out, bf16 W [N][K])
 // GEMV_ACT_SINUSOID: the input is the K-wide sinusoid of 1000 * x[b] (x [B]) instead.
-// clear, clear_n: words set to 0 by the launch (the GEMMs' split counters).
 enum { GEMV_ACT_NONE = 0, GEMV_ACT_SILU = 1, GEMV_ACT_SINUSOID = 2 };
 hipError_t launch_gemv(int32_t B, int32_t N, int32_t K, const float* x, int32_t act, const void* W,
-                       const float* bias, float* out, hipStream_t s, const int32_t* skip = nullptr,
-                       unsigned* clear = nullptr, int32_t clear_n = 0);
+                       const float* bias, float* out, hipStream_t s, const int32_t* skip = nullptr);
 // latent [B][C][F][Hl][Wl] bf16 -> tokens [B][F*Hg*Wg][C*4] bf16
 hipError_t launch_patchify(int32_t B, int32_t C, int32_t F, int32_t Hl, int32_t Wl,
                            const void* z, void* tok, hipStream_t s, const int32_t* skip = nullptr);

@@ -118,9 +118,22 @@ def test_block_kv_cache_equivalence_bitwise():
     """Three chunks in one block call (block-causal mask) equal three sequential cached
     calls, each appending its chunk's K/V (Figure 10b): every per-row computation is the
     same, so the results agree bit for bit."""
+    check_kv_cache_equivalence(synth.WORKLOADS["block_d512"].replace(n_cached=0))
+
+
+# the joint call's 903, 528 and 1632 rows take other tiles than the chunks' 301, 176 and 544
+@pytest.mark.parametrize("d,H,ffn,Hl,Wl,A,Lc", [(512, 8, 2048, 20, 26, 41, 19), (1536, 12, 8960, 16, 20, 16, 33),
+                                                (5120, 40, 13824, 32, 32, 32, 77)])
+def test_block_kv_cache_equivalence_bitwise_over_sizes(d, H, ffn, Hl, Wl, A, Lc):
+    """The same where the products of the joint call and of one chunk run in different tiles:
+    a row's bits depend on neither."""
+    check_kv_cache_equivalence(synth.WORKLOADS["block_d512"].replace(d=d, H=H, Dh=d // H, ffn=ffn, Hl=Hl, Wl=Wl, A=A,
+                                                                     Lc=Lc, n_cached=0))
+
+
+def check_kv_cache_equivalence(wl):
     import torch
     w = lib()
-    wl = synth.WORKLOADS["block_d512"].replace(n_cached=0)
     B, d, H, Dh, L, Lc = 1, wl.d, wl.H, wl.Dh, wl.L, wl.Lc
     W = {k: dev(v) for k, v in synth.block_params(wl, 3, 0.05, mod_std=0.3).items()}
     e0 = dev(synth.normal(0, "e0", (B, 6, d), 0.3, 3, dtype="f32"))
@@ -129,7 +142,7 @@ def test_block_kv_cache_equivalence_bitwise():
     pos = np.concatenate([w.wam_chunk_positions(c, wl.F, wl.Hg, wl.Wg, wl.A) for c in range(3)])
     cos, sin = (dev(a) for a in w.wam_rope_tables(pos, Dh))
     dims = dims_of(wl, 1)
-    log("block kv-cache equivalence")
+    log(f"block kv-cache equivalence d={d} L={L}")
     # one call, three query chunks
     kA = torch.zeros((B, 3 * L, H, Dh), dtype=torch.bfloat16, device="cuda")
     vA = torch.zeros_like(kA)

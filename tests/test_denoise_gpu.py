@@ -184,6 +184,35 @@ def test_denoise_loop_step_groups(B, steps):
     check_loop(case, list(np.linspace(0.0, 1.0, steps + 1)))
 
 
+@pytest.mark.parametrize("B,steps", [(1, 9), (2, 3)])
+def test_denoise_loop_equals_independent_steps(B, steps):
+    """The loop forms its time rows for several steps together and projects the text once:
+    bit for bit the state and velocities of single step calls followed by wam_flow_step,
+    also where the text products have few rows and a long K."""
+    import torch
+    w = lib()
+    case = LoopCase(small_wl(B=B, n_layers=2, text_dim=4096), 2)
+    ts = [float(np.float32(v)) for v in np.linspace(0.0, 1.0, steps + 1)]
+    log(f"denoise loop against steps B={B} steps={steps}")
+    s = case.gpu_loop_setup(ts)
+    x0 = s["x"].clone()
+    w.wam_denoise_chunk(case.model, s["io"], s["p"], s["ws"])
+    torch.cuda.synchronize()
+    vv, va, z, a, t = s["keep"]
+    got = [r.clone() for r in (s["x"], vv, va)]
+    x = s["x"].copy_(x0)
+    ws = workspace(w.wam_step_workspace_bytes(case.model, s["io"]))
+    dims = w.binding.wam_flow_dims(B=B, cfg=0, cfg_scale=1.0, n_video=case.nv, n_action=case.na)
+    w.wam_flow_step(dims, x, z, a, ts[0], ts[0])
+    for i in range(steps):
+        t.fill_(ts[i])
+        w.wam_dit_step_fwd(case.model, s["io"], ws)
+        w.wam_flow_step(dims, x, z, a, ts[i], ts[i + 1], v_video=vv, v_action=va)
+    torch.cuda.synchronize()
+    for name, p, q in zip(("state", "video", "action"), got, (x, vv, va)):
+        assert torch.equal(p, q), name
+
+
 def test_denoise_loop_guidance_pair():
     """Classifier-free guidance over a batch of two: sample 0 conditional, sample 1
     unconditional (different text and caches), one shared state."""

@@ -1,6 +1,5 @@
 """GPU parity of the GEMM's tile choices at the edges of their tiles: products that leave most
-of the chip idle in the largest tiles take smaller ones, and inside a call with a workspace
-the tiles past the last whole round are split over K."""
+of the chip idle in the largest tiles take smaller ones."""
 import numpy as np
 import pytest
 
@@ -45,16 +44,15 @@ def test_gemm_tile_edges(M, N, K):
     assert rel_l2(host(res)[rows] - x0.f64[rows], ref) <= 1e-5
 
 
-# d=512: FFN2's 64x64 tiles split; d=1280 with a wide FFN: 128x128 tiles in several parts, odd rows
+# a wide FFN and a short one, odd rows: products of few tiles and many K slices
 @pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("d,H,ffn,Hl,Wl,A,Lc", [(512, 8, 2048, 10, 14, 3, 19), (1280, 10, 8960, 18, 34, 7, 33)])
-def test_block_split_products(d, H, ffn, Hl, Wl, A, Lc, fp8):
-    """A block whose products split over K against the fp64 oracle (2e-2; FP8 projections of
-    the unquantized model: 0.1), three runs bitwise equal (the parts finish in another order
-    each time, their sum is taken in one order)."""
+def test_block_few_rows(d, H, ffn, Hl, Wl, A, Lc, fp8):
+    """A block of few rows against the fp64 oracle (2e-2; FP8 projections of the unquantized
+    model: 0.1), three runs bitwise equal."""
     wl = synth.WORKLOADS["block_d512"].replace(d=d, H=H, Dh=d // H, ffn=ffn, Hl=Hl, Wl=Wl, A=A, Lc=Lc, n_cached=1,
                                                mod_std=0.3)
-    log(f"split block d={d} L={wl.L} fp8={fp8}")
+    log(f"few-row block d={d} L={wl.L} fp8={fp8}")
     case = BlockCase(wl, bias_std=0.05)
     x, kc, vc = case.run_gpu(fp8=fp8)
     rx, _, _ = case.run_oracle()
