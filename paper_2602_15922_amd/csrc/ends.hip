@@ -23,8 +23,8 @@ WAM_DEV f32x4m mfma16(bf16x8 a, bf16x8 b, f32x4m c) {
 // the patch gathered straight from the latents: a lane's token's (pw) pairs are 4-byte loads,
 // consecutive tokens consecutive.  A lane of the product has one column of 16 tokens, so
 // every store instruction writes two whole 128-byte lines.  Bound by the 4 d bytes written
-// per row: at 3152 x 5120 the patchify, the two products and their launches took 34 us, this
-// kernel 18 (3.6 TB/s).
+// per row: at 3152 x 5120 the patchify, the two products and their launches took 34 us in the
+// present GEMM tiles, this kernel 19 (3.4 TB/s).
 // ---------------------------------------------------------------------------------
 constexpr int EMB_COLS = 256;  // columns per workgroup, 64 per wavefront
 
@@ -106,16 +106,19 @@ __global__ __launch_bounds__(256) void embed_kernel(const EmbedArgs a, int tiles
 // action rows), the video features put back as pixels.  A workgroup of 8 wavefronts takes 16
 // rows of one kind, two per wavefront, held in registers between the mean, variance and
 // output passes, so x is read once.  The product runs over chunks of 256 columns with one
-// barrier each: h of the chunk goes to LDS (two buffers), its 64 rows of W come by direct loads
-// into a ring of three stages, and each wavefront multiplies one k-step of 32 columns
-// (16x16x32 MFMA); the wavefronts' sums are added through LDS at the end.  (W straight from
+// barrier each: h of the chunk goes to LDS, its 64 rows of W come by direct loads into a ring of
+// three stages, and wavefronts 0 to 3 multiply 16 outputs each (16x16x32 MFMA).  Every sum is
+// taken in the order of the general path, so the velocities are bit for bit those of the modulated
+// LayerNorm, the GEMM's fp32 epilogue and the unpatchify: a lane holds the columns it holds in
+// the LayerNorm of that width (V8: 8 consecutive ones, 512 per step of the row, which are
+// two chunks of h), and one wavefront runs an output's whole K.  (W straight from
 // L2 into MFMA operands, 16 rows of 64 bytes per load, takes a cycle per lane in the address
 // path: 44 us at 3152 x 5120, 55 with 8 rows per workgroup.)  Bound by the 4 d bytes read per
 // row, then by the W reads (640 KB per workgroup at 64 bytes per cycle): the LayerNorm (a
 // bf16 h written and read again), the products of 64 and 16 columns and the unpatchify took
-// 53 us there, this kernel 25.
+// 53 us there in the present GEMM tiles (117 in 128-row tiles), this kernel 26.
 // ---------------------------------------------------------------------------------
-constexpr int HEAD_ROWS = 16, HEAD_CH = 256, HEAD_N = 64, HEAD_STAGES = 3;
+constexpr int HEAD_ROWS = 16, HEAD_CH = 256, HEAD_N = 64, HEAD_STAGES = 3, HEAD_HBUFS = 3;
 constexpr int HEAD_WSTAGE = HEAD_N * HEAD_CH * 2, HEAD_HBUF = HEAD_ROWS * HEAD_CH * 2;  // bytes
 
 typedef __attribute__((address_space(3))) void lds_void;
@@ -124,11 +127,12 @@ typedef __attribute__((address_space(3))) void lds_void;
 // fragment read touches would share their banks)
 WAM_DEV int head_swz(int r, int c) { return r * (HEAD_CH * 2) + ((c ^ (r & 15)) << 4); }
 
-template <int NV>  // float4s of a row per lane = chunks of 256 columns (at least d / 256)
+// NV: float4s of a row per lane = chunks of 256 columns (at least d / 256); V8: d a multiple of 512
+template <int NV, bool V8>
 __global__ __launch_bounds__(512, 2) void head_kernel(const HeadArgs a) {
   // W ring, h buffers, then the folded modulation P = 1 + scale and Q = shift; one array, so
   // that the compiler does not hold LDS reads back for the direct loads in flight
-  constexpr int HS = HEAD_STAGES * HEAD_WSTAGE, PQ = HS + 2 * HEAD_HBUF;
+  constexpr int HS = HEAD_STAGES * HEAD_WSTAGE, PQ = HS + HEAD_HBUFS * HEAD_HBUF;
   __shared__ __attribute__((aligned(16))) char smem[PQ + 2 * NV * HEAD_CH * 4];
   if (skip_step(a.skip)) return;
   const int lane = threadIdx.x & 63, l16 = lane & 15, q4 = lane >> 4;
@@ -146,7 +150,10 @@ __global__ __launch_bounds__(512, 2) void head_kernel(const HeadArgs a) {
     const int row = first + 2 * w + r < count ? first + 2 * w + r : count - 1;
 #pragma unroll
     for (int i = 0; i < NV; ++i)
-      if (i < nv) v[r][i] = *reinterpret_cast<const f32x4*>(x + (int64_t)row * d + (i * 64 + lane) * 4);
+      if (i < nv) {
+        const int col = V8 ? ((i >> 1) * 64 + lane) * 8 + (i & 1) * 4 : (i * 64 + lane) * 4;
+        v[r][i] = *reinterpret_cast<const f32x4*>(x + (int64_t)row * d + col);
+      }
   }
   float* P = reinterpret_cast<float*>(smem + PQ);
   float* Q = P + d;
@@ -200,44 +207,66 @@ __global__ __launch_bounds__(512, 2) void head_kernel(const HeadArgs a) {
       }
     rstd[r] = rsqrtf(wave_sum(q) / (float)d + a.eps);
   }
-  f32x4m acc[HEAD_N / 16];
-#pragma unroll
-  for (int n = 0; n < HEAD_N / 16; ++n) acc[n] = f32x4m{0.f, 0.f, 0.f, 0.f};
+  f32x4m acc = {0.f, 0.f, 0.f, 0.f};  // of outputs 16 w .. 16 w + 15 (wavefronts 0 to 3)
+  const bool mul = 16 * w < N;
   __syncthreads();  // P and Q
 #pragma unroll
   for (int c = 0; c < NV; ++c) {
     if (c < nv) {
-      char* hb = smem + HS + (c & 1) * HEAD_HBUF;
-      const f32x4 pp = *reinterpret_cast<const f32x4*>(P + HEAD_CH * c + 4 * lane);
-      const f32x4 qq = *reinterpret_cast<const f32x4*>(Q + HEAD_CH * c + 4 * lane);
+      if (!V8 || c % 2 == 0) {
+        // this lane's columns of chunk c, or of chunks c (lanes 0 to 31) and c + 1 (the others)
+        constexpr int E = V8 ? 2 : 1;  // float4s
+        const int col = V8 ? HEAD_CH * c + 8 * lane : HEAD_CH * c + 4 * lane;
+        const int buf = V8 && lane >= 32 ? (c + 1) % HEAD_HBUFS : c % HEAD_HBUFS;
+        char* hb = smem + HS + buf * HEAD_HBUF;
+        bf16 o[2][4 * E];
 #pragma unroll
-      for (int r = 0; r < 2; ++r) {
-        bf16x4 o;
+        for (int f = 0; f < E; ++f) {
+          const f32x4 pp = *reinterpret_cast<const f32x4*>(P + col + 4 * f);
+          const f32x4 qq = *reinterpret_cast<const f32x4*>(Q + col + 4 * f);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = (bf16)((v[r][c][e] - mean[r]) * rstd[r] * pp[e] + qq[e]);
-        *reinterpret_cast<bf16x4*>(hb + head_swz(2 * w + r, lane >> 1) + 8 * (lane & 1)) = o;
+          for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[r][4 * f + e] = (bf16)((v[r][c + f][e] - mean[r]) * rstd[r] * pp[e] + qq[e]);
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+          if constexpr (V8) {
+            bf16x8 t;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) t[e] = o[r][e];
+            *reinterpret_cast<bf16x8*>(hb + head_swz(2 * w + r, lane & 31)) = t;
+          } else {
+            bf16x4 t;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t[e] = o[r][e];
+            *reinterpret_cast<bf16x4*>(hb + head_swz(2 * w + r, lane >> 1) + 8 * (lane & 1)) = t;
+          }
+        }
       }
       // h written, this wavefront's part of W's chunk c landed (chunk c + 1 may be in flight);
-      // past the barrier both are everyone's, and the stage of chunk c - 1 is free
+      // past the barrier both are everyone's, and the stage and the h buffer of chunk c - 1 are free
       __builtin_amdgcn_s_waitcnt(4 | (7 << 4) | (0 << 8));  // vmcnt(4), lgkmcnt(0)
       asm volatile("" ::: "memory");
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
       fetch(c + 2);
-      const char* ws = smem + (c % HEAD_STAGES) * HEAD_WSTAGE;
-      const bf16x8 h = *reinterpret_cast<const bf16x8*>(hb + head_swz(l16, 4 * w + q4));
+      if (mul) {
+        const char* hb = smem + HS + (c % HEAD_HBUFS) * HEAD_HBUF;
+        const char* ws = smem + (c % HEAD_STAGES) * HEAD_WSTAGE;
 #pragma unroll
-      for (int n = 0; n < HEAD_N / 16; ++n)
-        acc[n] = mfma16(h, *reinterpret_cast<const bf16x8*>(ws + head_swz(16 * n + l16, 4 * w + q4)), acc[n]);
+        for (int ks = 0; ks < HEAD_CH / 32; ++ks)
+          acc = mfma16(*reinterpret_cast<const bf16x8*>(hb + head_swz(l16, 4 * ks + q4)),
+                       *reinterpret_cast<const bf16x8*>(ws + head_swz(16 * w + l16, 4 * ks + q4)), acc);
+      }
     }
   }
   __builtin_amdgcn_s_waitcnt(0);  // the ring's last loads land before its LDS is reused
   __syncthreads();
-  float* red = reinterpret_cast<float*>(smem);  // [8 wavefronts][16 rows][64]
+  float* red = reinterpret_cast<float*>(smem);  // [16 rows][64]
+  if (mul)
 #pragma unroll
-  for (int n = 0; n < HEAD_N / 16; ++n)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) red[(w * HEAD_ROWS + 4 * q4 + r) * HEAD_N + 16 * n + l16] = acc[n][r];
+    for (int r = 0; r < 4; ++r) red[(4 * q4 + r) * HEAD_N + 16 * w + l16] = acc[r];
   __syncthreads();
   const float* bias = video ? a.b_hv : a.b_ha;
   for (int o = threadIdx.x; o < HEAD_ROWS * N; o += 512) {
@@ -252,10 +281,7 @@ __global__ __launch_bounds__(512, 2) void head_kernel(const HeadArgs a) {
       n = o - m * N;
     }
     if (first + m >= count) continue;
-    float s = 0.f;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) s += red[(k * HEAD_ROWS + m) * HEAD_N + n];
-    s += bias ? bias[n] : 0.f;
+    const float s = red[m * HEAD_N + n] + (bias ? bias[n] : 0.f);
     const int tok = first + m;
     if (video) {
       const int sx = tok % Wg, r = (tok / Wg) % Hg, fr = tok / (Wg * Hg);
@@ -285,9 +311,15 @@ hipError_t launch_head(const HeadArgs& a, hipStream_t s) {
   const int Lv = a.F * (a.Hl / 2) * (a.Wl / 2);
   const dim3 grid((unsigned)(a.B * ((Lv + HEAD_ROWS - 1) / HEAD_ROWS + (a.A + HEAD_ROWS - 1) / HEAD_ROWS))), block(512);
   const int nv = a.d / 256;
-  if (nv <= 4) hipLaunchKernelGGL((head_kernel<4>), grid, block, 0, s, a);
-  else if (nv <= 12) hipLaunchKernelGGL((head_kernel<12>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((head_kernel<20>), grid, block, 0, s, a);
+  if (nv % 2 == 0) {
+    if (nv <= 4) hipLaunchKernelGGL((head_kernel<4, true>), grid, block, 0, s, a);
+    else if (nv <= 12) hipLaunchKernelGGL((head_kernel<12, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((head_kernel<20, true>), grid, block, 0, s, a);
+  } else {
+    if (nv <= 3) hipLaunchKernelGGL((head_kernel<3, false>), grid, block, 0, s, a);
+    else if (nv <= 11) hipLaunchKernelGGL((head_kernel<11, false>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((head_kernel<19, false>), grid, block, 0, s, a);
+  }
   return hipGetLastError();
 }
 

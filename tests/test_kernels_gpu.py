@@ -281,3 +281,52 @@ def test_embed_and_head_sizes(d, H, C, act_dim, F, Hl, Wl, A, B):
     assert rel_l2(host(vs), rv) <= 5e-3
     assert A == 0 or rel_l2(host(va), ra) <= 5e-3
     assert (host(vv[-8:]) == -7).all()
+
+
+@pytest.mark.parametrize("d,H,C,act_dim,F,Hl,Wl,A,B", [
+    (256, 2, 16, 16, 1, 4, 6, 3, 1),        # one chunk of columns
+    (512, 8, 16, 16, 2, 6, 10, 17, 2),      # two chunks, ragged row tiles of both kinds
+    (1280, 10, 4, 48, 1, 6, 10, 17, 1),     # an odd number of chunks
+    (3072, 24, 12, 64, 1, 10, 14, 5, 2),    # 48 and 64 outputs, the next register tier
+    (4864, 38, 16, 16, 1, 6, 6, 20, 1),     # an odd number of chunks in the largest tier
+    (5120, 40, 16, 16, 2, 10, 14, 33, 2),   # the widest rows
+])
+def test_embed_and_head_equal_their_parts(d, H, C, act_dim, F, Hl, Wl, A, B):
+    """The one-launch embedding and head give, bit for bit, what the library's own products
+    give on gathered patches, and its modulated LayerNorm, products and unpatchify: every
+    sum in the same order, whatever the number of rows."""
+    import torch
+    w = lib()
+    wl = synth.WORKLOADS["block_d512"].replace(d=d, H=H, Dh=d // H, latent_ch=C, act_dim=act_dim, F=F, Hl=Hl, Wl=Wl,
+                                               A=A, B=B)
+    log(f"ends against their parts d={d} C={C} act_dim={act_dim} L={wl.L}")
+    P, top, m = small_model(wl)
+    L, Lv, Hg, Wg = wl.L, wl.Lv, Hl // 2, Wl // 2
+    z = dev(synth.normal(wl.seed, "z_t", (B, C, F, Hl, Wl), 1.0))
+    a = dev(synth.normal(wl.seed, "a_t", (B, A, act_dim), 1.0))
+    x = torch.empty((B, L, d), dtype=torch.float32, device="cuda")
+    w.wam_embed_fwd(m, z, a, x, workspace(w.wam_embed_workspace_bytes(m.dims, B, F, Hl, Wl)))
+    tok = z.view(B, C, F, Hg, 2, Wg, 2).permute(0, 2, 3, 5, 1, 4, 6).reshape(B * Lv, 4 * C).contiguous()
+    xv = torch.empty((B * Lv, d), dtype=torch.float32, device="cuda")
+    xa = torch.empty((B * A, d), dtype=torch.float32, device="cuda")
+    w.wam_gemm_bf16(tok, top["w_patch"], xv, w.WAM_EPI_F32, bias=top["b_patch"])
+    w.wam_gemm_bf16(a.view(B * A, act_dim), top["w_ain"], xa, w.WAM_EPI_F32, bias=top["b_ain"])
+    torch.cuda.synchronize()
+    assert torch.equal(x, torch.cat((xv.view(B, Lv, d), xa.view(B, A, d)), 1))
+    x = x * 3.0 + dev(synth.normal(wl.seed, "x", (B, L, d), 0.5, dtype="f32"))
+    e = dev(synth.normal(wl.seed, "e0", (B, d), 0.3, dtype="f32"))
+    vv = torch.empty((B, C, F, Hl, Wl), dtype=torch.float32, device="cuda")
+    va = torch.empty((B, A, act_dim), dtype=torch.float32, device="cuda")
+    w.wam_head_fwd(m, x, e, vv, va, workspace(w.wam_head_workspace_bytes(m.dims, B, F, Hl, Wl, A)))
+    h = torch.empty((B, L, d), dtype=torch.bfloat16, device="cuda")
+    mod2 = top["head_mod2"]
+    w.wam_adaln_ln_mod(x, h, wl.eps, L, shift_a=mod2[0], shift_v=e, scale_a=mod2[1], scale_v=e, mod_stride=d)
+    hv, ha = h[:, :Lv].reshape(B * Lv, d).contiguous(), h[:, Lv:].reshape(B * A, d).contiguous()
+    pv = torch.empty((B * Lv, 4 * C), dtype=torch.float32, device="cuda")
+    pa = torch.empty((B * A, act_dim), dtype=torch.float32, device="cuda")
+    w.wam_gemm_bf16(hv, top["w_hv"], pv, w.WAM_EPI_F32, bias=top["b_hv"])
+    w.wam_gemm_bf16(ha, top["w_ha"], pa, w.WAM_EPI_F32, bias=top["b_ha"])
+    torch.cuda.synchronize()
+    pix = pv.view(B, F, Hg, Wg, C, 2, 2).permute(0, 4, 1, 2, 5, 3, 6).reshape(B, C, F, Hl, Wl)
+    assert torch.equal(va, pa.view(B, A, act_dim))
+    assert torch.equal(vv, pix)
