@@ -216,16 +216,23 @@ WAM_DEV void fetch_slice(char* smem, int buf, const GemmLane<C>& L, int kt, int 
   char* As = smem + buf * C::STAGE;
   char* Bs = As + C::BM * C::ROWB;
   const int k0 = kt * C::BK, soff = C::EB * k0;
-  const bool full = FULL || k0 + C::BK <= K;
+  if (FULL || k0 + C::BK <= K) {
 #pragma unroll
-  for (int i = LO; i < HI; ++i) {
-    if (i < C::NIA) {
-      const int sh = full || k0 + L.kla[i] < K ? 0 : C::EB * (K - C::EPC - L.kla[i] - k0);
-      load_lds16(ra, As + (L.w * C::NIA + i) * 1024, L.a_off[i] + sh, soff);
-    } else {
-      const int c = i - C::NIA;
-      const int sh = full || k0 + L.klb[c] < K ? 0 : C::EB * (K - C::EPC - L.klb[c] - k0);
-      load_lds16(rb, Bs + (L.w * C::NIB + c) * 1024, L.b_off[c] + sh, soff);
+    for (int i = LO; i < HI; ++i) {
+      if (i < C::NIA) load_lds16(ra, As + (L.w * C::NIA + i) * 1024, L.a_off[i], soff);
+      else load_lds16(rb, Bs + (L.w * C::NIB + i - C::NIA) * 1024, L.b_off[i - C::NIA], soff);
+    }
+  } else {
+#pragma unroll
+    for (int i = LO; i < HI; ++i) {
+      if (i < C::NIA) {
+        const int sh = k0 + L.kla[i] < K ? 0 : C::EB * (K - C::EPC - L.kla[i] - k0);
+        load_lds16(ra, As + (L.w * C::NIA + i) * 1024, L.a_off[i] + sh, soff);
+      } else {
+        const int c = i - C::NIA;
+        const int sh = k0 + L.klb[c] < K ? 0 : C::EB * (K - C::EPC - L.klb[c] - k0);
+        load_lds16(rb, Bs + (L.w * C::NIB + c) * 1024, L.b_off[c] + sh, soff);
+      }
     }
   }
 }
@@ -329,7 +336,10 @@ WAM_DEV void block_barrier() {
 // run while slice t+S is fetched into stage CUR and k-step 0 of slice t+1 is read.  No
 // wave waits on an LDS read right after the barrier.
 // (With C::NFIRST < NL the fetch is spread: its first loads are issued there, the rest in
-// the first k-steps of slice t+1.)
+// the first k-steps of slice t+1.  A fetch issued whole, in the 2-stage tiles, keeps the branch
+// on the slice's end, which fences it ahead of the MFMAs: with its loads scheduled among them
+// those tiles take 1-5% longer (2900 x 3072 x 12288 in 192x256 tiles 237 against 228 us, FP8
+// 880 x 13824 x 5120 in 256x256 tiles 82.6 against 79.0).)
 // (Block-scaled A: ering[stage] holds the exponents of the slice in that stage.  Slice
 // t+S's exponents are loaded after slice t's last MFMAs, so they take the same registers:
 // loaded any earlier, both values are live at once and the compiler moves registers at
@@ -366,7 +376,8 @@ WAM_DEV void slice_steady(char* smem, const GemmLane<C>& L, int t, int K, f32x16
   WAM_WAIT_VMCNT((S - 2) * NI);
   block_barrier();
   __builtin_amdgcn_sched_barrier(0);
-  fetch_slice<C, true, 0, C::NFIRST>(smem, CUR, L, !C::MXA || t + S < nk ? t + S : nk - 1, K);
+  if constexpr (C::MXA) fetch_slice<C, true, 0, C::NFIRST>(smem, CUR, L, t + S < nk ? t + S : nk - 1, K);
+  else fetch_slice<C, (C::NFIRST < C::NL), 0, C::NFIRST>(smem, CUR, L, t + S, K);
   read_frags<C>(smem, (CUR + 1) % S, L, 0, fa[KS & 1], fb[KS & 1]);
   mfma_step<C>(fa[(KS - 1) & 1], fb[(KS - 1) & 1], acc, ering[CUR], KS - 1);
   interleave_step<NMF, NR, C::NFIRST>();
