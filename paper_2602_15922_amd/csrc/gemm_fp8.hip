@@ -11,6 +11,7 @@ namespace {
 struct Fp8Tiles {
   using C64 = Cfg<64, 64, 128, 4, 2, 2, 2, 1, 2, 2>;
   using C128 = Cfg<128, 128, 128, 4, 4, 2, 2, 1, 2, 2>;
+  using C128x2 = Cfg<128, 128, 128, 2, 2, 2, 2, 1>;
   using C192n = Cfg<192, 128, 128, 3, 2, 4, 2, 1, 3, 2>;
   using C288 = void;  // for wide products such as FFN1, whose block-scaled output its 32-column waves cannot write
   using C128w = Cfg<128, 256, 128, 3, 2, 4, 2, 1, 3, 3>;

@@ -24,18 +24,12 @@
 #include <type_traits>
 
 #include "common.h"
+#include "gemm_plan.h"
 #include "kernels.h"
 
 namespace wam {
 int cu_count();
 
-// The tiles a product can run in (rows x columns; gemm_tiles.h's users instantiate each for
-// their operand type), and how a launch deals them.
-enum GemmTile { TILE_64x64, TILE_128x128, TILE_192x128, TILE_288x128, TILE_128x256, TILE_192x256, TILE_256x256, NTILES };
-struct GemmPlan {
-  int tile = TILE_128x256;
-  int two = -1, c1 = 0;  // two column ranges: c1 columns of `tile`, the rest in tile `two`
-};
 hipError_t launch_gemm_fp8(const GemmArgs& g, const GemmPlan& p, const GemmGroup* gg, hipStream_t s);
 namespace {
 
@@ -870,6 +864,7 @@ hipError_t launch_plan(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
     // the block-scaled output needs a wave's columns to be one 64-column block
     case TILE_64x64: if constexpr (EPI != WAM_EPI_GELU_MX8) return launch_one<typename T::C64, EPI>(g, s); break;
     case TILE_128x128: return launch_one<typename T::C128, EPI>(g, s);
+    case TILE_128x128_2: return launch_one<typename T::C128x2, EPI>(g, s);
     case TILE_192x128: if constexpr (EPI != WAM_EPI_GELU_MX8) return launch_one<typename T::C192n, EPI>(g, s); break;
     case TILE_288x128: if constexpr (!std::is_void<typename T::C288>::value) return launch_one<typename T::C288, EPI>(g, s); break;
     case TILE_128x256: return launch_one<typename T::C128w, EPI>(g, s);
@@ -884,6 +879,7 @@ hipError_t launch_group_plan(const GemmArgs& g, const GemmPlan& p, const GemmGro
   switch (p.tile) {
     case TILE_64x64: return launch_grouped<typename T::C64>(g, gg, s);
     case TILE_128x128: return launch_grouped<typename T::C128>(g, gg, s);
+    case TILE_128x128_2: return launch_grouped<typename T::C128x2>(g, gg, s);
     case TILE_192x128: return launch_grouped<typename T::C192n>(g, gg, s);
     case TILE_288x128: if constexpr (!std::is_void<typename T::C288>::value) return launch_grouped<typename T::C288>(g, gg, s); break;
     case TILE_128x256: return launch_grouped<typename T::C128w>(g, gg, s);

@@ -102,7 +102,7 @@ def test_ln_mod_fp8_rejects_widths_it_does_not_take():
         w.wam_adaln_ln_mod_fp8(x, q, s, 1e-6, 2)
 
 
-GEMM_SHAPES = [(300, 200, 144), (3152, 5192, 528), (17, 16, 16), (3152, 13700, 144)]  # the last: two column ranges
+GEMM_SHAPES = [(300, 200, 144), (3152, 5192, 528), (17, 16, 16), (3152, 13700, 144)]
 
 
 @pytest.mark.parametrize("M,N,K", GEMM_SHAPES)
@@ -201,7 +201,10 @@ def codes_dev(vals):
     return torch.from_numpy(np.ascontiguousarray(vals)).to(torch.float8_e4m3fn).view(torch.uint8).cuda()
 
 
-MXA_SHAPES = [(300, 200, 512), (1000, 640, 384), (37, 256, 128), (129, 256, 256), (3152, 5120, 13824)]
+MXA_SHAPES = [(300, 200, 512), (1000, 640, 384), (37, 256, 128), (129, 256, 256), (3152, 5120, 13824),
+              # one per tile and pair of column ranges that takes it, ragged
+              (300, 3040, 1152), (325, 5472, 1152), (389, 8232, 1152), (385, 11016, 2048), (516, 13064, 1152),
+              (770, 13104, 1536), (385, 11032, 1152), (1026, 14520, 1152), (1794, 13080, 1536), (1538, 12304, 2560)]
 
 
 @pytest.mark.parametrize("M,N,K", MXA_SHAPES)
@@ -212,7 +215,8 @@ def test_gemm_fp8_block_scaled_a(M, N, K, epi):
     from block to block, against the oracle's fp64 product of the decoded blocks times the
     per-channel W scales (fp32 accumulation and the bf16 output rounding remain).  The
     shapes cover one, two and three slices of 128 columns (fewer than the prefetch ring's
-    stages), ragged row and column tiles, and the FFN2 shape (oracle on sampled rows)."""
+    stages), ragged row and column tiles, the FFN2 shape and every tile (oracle on sampled
+    rows)."""
     import torch
     w = lib()
     log(f"gemm fp8 block-scaled A {epi} M={M} N={N} K={K}")
@@ -257,7 +261,10 @@ def sampled_rows(M):
     return np.array(sorted(i for i in r if 0 <= i < M))
 
 
-MX8_SHAPES = [(300, 512, 512), (130, 1280, 256), (3152, 13824, 5120)]
+MX8_SHAPES = [(300, 512, 512), (130, 1280, 256),
+              # one per tile and pair of column ranges that takes it, ragged rows
+              (513, 6656, 1152), (519, 6656, 1552), (1156, 6656, 1152), (1732, 6528, 1536), (1032, 14592, 1152),
+              (1345, 14208, 2064), (3152, 13824, 5120)]
 
 
 @pytest.mark.parametrize("M,N,K", MX8_SHAPES)

@@ -76,14 +76,18 @@ def test_rope_qkv_and_cache_append(Dh, H, B, L, c):
 # ----------------------------------------------------------------------------- GEMM epilogues
 GEMM_SHAPES = [
     (300, 200, 136),     # small tiles, ragged M, N and K (K % 64 != 0)
-    (3152, 5100, 520),   # 128x256 tiles (500 of them, 2 rounds), ragged M, N and K
+    (3152, 5100, 520),   # two 128x128 workgroups per CU in two rounds, ragged M, N and K
     (17, 16, 16),        # the action embedding's K
     (130, 203, 72),      # N % 4 != 0: the last column group is stored element by element
     (1000, 12700, 520),  # 256x256 tiles (200, one round), ragged M, N and K
     (570, 15300, 136),   # 192x256 tiles (180, one round, against 300 of 128 rows), ragged M, N and K
-    (3152, 13700, 136),  # two column ranges in one launch: 39 columns of 256-row tiles, 15 of 192
-    (1347, 16590, 72),   # two column ranges: 256- and 128-row tiles
-    (903, 16590, 136),   # two column ranges: 192- and 128-row tiles
+    (3152, 13700, 136),  # a wide N and a short K in 128x128 tiles, many rounds
+    (1347, 16590, 72),
+    (903, 16590, 136),
+    (778, 6534, 776),    # 128x256 tiles
+    (1798, 13078, 776),  # two column ranges in one launch: 32 columns of 256-row tiles, 20 of 192
+    (2305, 8206, 1032),  # two column ranges: 256- and 128-row tiles
+    (1025, 14606, 584),  # two column ranges: 192- and 128-row tiles
 ]
 
 
