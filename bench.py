@@ -19,6 +19,7 @@ denoising loop and the step with FP8 projections on the same model.
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -603,11 +604,15 @@ def pmc_summary(path):
               + f" | {util} | {clk} |")
 
 
+# The kernel that opens a step: the time MLP's first layer, which forms the sinusoid itself.
+STEP_OPENS = re.compile(r"gemv_kernel<\d+, \d+, true>")
+
+
 def trace_summary(path, steps):
     """Kernel time by (kernel, grid size) from a rocprofv3 kernel-trace CSV: calls, average,
     min and max duration, total, share of all kernel time, and (steps > 0) milliseconds per
     step over the dispatches of the run's last `steps` steps, a step being delimited by
-    the time-embedding kernel that opens it."""
+    the time-embedding kernel that opens it.  A trace with fewer steps is an error."""
     import csv
     import glob
     files = sorted(glob.glob(os.path.join(path, "**", "*kernel_trace.csv"), recursive=True))
@@ -621,11 +626,10 @@ def trace_summary(path, steps):
     rows.sort()
     total = sum(e - b for b, e, _, _ in rows)
     if steps > 0:
-        starts = [i for i, r in enumerate(rows) if r[2].startswith("sinusoid_kernel")]
-        if len(starts) >= steps:
-            rows_s = rows[starts[-steps]:]
-        else:
-            rows_s = rows
+        starts = [i for i, r in enumerate(rows) if STEP_OPENS.search(r[2])]
+        if len(starts) < steps:
+            sys.exit(f"{len(starts)} steps in the trace under {path}, {steps} asked for")
+        rows_s = rows[starts[-steps]:]
     agg = {}
     for b, e, n, g in rows:
         a = agg.setdefault((n, g), [0, 0, 1e18, 0])
