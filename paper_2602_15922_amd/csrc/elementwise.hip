@@ -465,9 +465,10 @@ __global__ __launch_bounds__(256) void rope_qkv_fp8_kernel(const RopeFp8Args f) 
 // k of each of its wavefront's W rows per 16-byte load, so W streams from HBM once with
 // the first steps' loads in flight while the input is staged.  Lane l sums k = 8 l + 512 i (+0..7), the same
 // order for any pass length (passes are multiples of 512 columns).  WR = 4 for the wide
-// layers (fewer stagings of the input), 2 where 16 features per workgroup leave fewer than four
-// workgroups per CU.  At B = 1: 5120 x 5120 15.2 -> 12.5 us, 30720 x 5120 58.4 -> 55.0 us (5.7
-// TB/s), with the first W loads ahead of the staging instead of after it.
+// layers (fewer stagings of the input, and fewer LDS reads of it per W row, which bound several
+// samples), 2 for the narrow ones (more workgroups; the rule is in launch_gemv).  At B = 1: 5120
+// x 5120 15.2 -> 11.9 us, 30720 x 5120 58.2 -> 55.2 us (5.7 TB/s), with the first W loads ahead of
+// the staging instead of after it; at B = 8 52.4 -> 49.5 and 205 -> 187.
 // GEMV_ACT_SINUSOID: the input is the timestep embedding of t = x[b], [cos(1000 t w_k), sin(1000
 // t w_k)], w_k = 10000^(-k/half), evaluated in every workgroup's staging (in double, so the
 // large arguments, up to 1000 rad, keep full fp32 accuracy).
@@ -712,7 +713,10 @@ hipError_t launch_gemv(int32_t B, int32_t N, int32_t K, const float* x, int32_t 
   if (B > GEMV_MAXB || K % 8 != 0) return hipErrorInvalidValue;
   const bf16* w = static_cast<const bf16*>(W);
   if (act == GEMV_ACT_SINUSOID) return launch_gemv_rows<2, true>(B, N, K, x, act, w, bias, out, s, skip);
-  if (N < 64 * cu_count()) return launch_gemv_rows<2, false>(B, N, K, x, act, w, bias, out, s, skip);
+  // two rows per wavefront: up to 24 features per CU for one sample (5120 x 5120 11.9 us against
+  // 14.4 with four, 9216 x 1536 11.6 against 8.7), up to 12 for several (at B = 8 3072 x 512 8.6
+  // against 10.2, 5120 x 5120 76.8 against 49.5)
+  if (N <= (B == 1 ? 24 : 12) * cu_count()) return launch_gemv_rows<2, false>(B, N, K, x, act, w, bias, out, s, skip);
   return launch_gemv_rows<4, false>(B, N, K, x, act, w, bias, out, s, skip);
 }
 
