@@ -184,8 +184,8 @@ def test_time_embedding():
 @pytest.mark.parametrize("B,d", [(1, 512), (5, 512), (8, 768), (2, 2816)])
 def test_time_embedding_sizes(B, d):
     """The time MLP's kernel over its edges: one sample, an odd count, the most (8); widths
-    whose 6 d outputs lie on both sides of the switch of the rows per workgroup (16384), and
-    K not a multiple of a pass (512).  The tolerance is the plain case's: fp32 sums of at most
+    whose 6 d outputs lie on both sides of the switch of the rows per wavefront (6144 for one
+    sample, 3072 for several), and K not a multiple of a pass (512).  The tolerance is the plain case's: fp32 sums of at most
     2816 terms (2816 * 6e-8 = 1.7e-4 of the terms' magnitudes at the very worst) and the
     sinusoid's argument, up to 1000, rounded to fp32 (6e-5)."""
     import torch
@@ -202,6 +202,43 @@ def test_time_embedding_sizes(B, d):
     re, re0 = oracle.time_embedding(t.f64, f["w_t1"], f["b_t1"], f["w_t2"], f["b_t2"], f["w_t6"], f["b_t6"])
     assert rel_l2(host(e), re) <= 1e-4
     assert rel_l2(host(e0), re0) <= 1e-4
+
+
+@pytest.mark.parametrize("B,d,freq_dim", [
+    (8, 2304, 256),    # 2 rows per wavefront, K in two passes, the last of 256 columns
+    (8, 2816, 256),    # a last pass of 768 columns; 4 rows per wavefront in the last layer
+    (4, 5120, 256),    # 4 rows per wavefront throughout, a pass of 4096 columns and one of 1024
+    (5, 5120, 264),    # a pass of 3072, then 2048; the sinusoid's K not a multiple of a lane's step
+    (8, 512, 2560),    # the sinusoid itself in two passes
+    (7, 4864, 1000),   # odd batch, ragged passes of every layer
+])
+def test_time_embedding_in_passes(B, d, freq_dim):
+    """Inputs that do not fit LDS at once (B * K > 16384 floats) are staged in passes: against
+    the oracle (1e-4 as above; 5120 terms) and, bit for bit, each sample as a call of its own
+    gives it, which the denoising loop's grouped time rows rely on."""
+    import torch
+    w = lib()
+    wl = synth.WORKLOADS["block_d512"].replace(B=B, d=d, H=d // 64, freq_dim=freq_dim)
+    P, top, m = small_model(wl)
+    t = synth.uniform(wl.seed, "t", (B,))
+    log(f"time embedding in passes B={B} d={d} freq_dim={freq_dim}")
+    ws = workspace(w.wam_time_embed_workspace_bytes(m.dims, B))
+    td = dev(t)
+    e = torch.full((B, d), float("nan"), dtype=torch.float32, device="cuda")
+    e0 = torch.full((B, 6, d), float("nan"), dtype=torch.float32, device="cuda")
+    w.wam_time_embed_fwd(m, td, e, e0, ws)
+    torch.cuda.synchronize()
+    f = {k: v.f64 for k, v in P.items()}
+    sinus = oracle.timestep_sinusoid(t.f64, freq_dim)
+    re = oracle.linear(oracle.silu(oracle.linear(sinus, f["w_t1"], f["b_t1"])), f["w_t2"], f["b_t2"])
+    re0 = oracle.linear(oracle.silu(re), f["w_t6"], f["b_t6"]).reshape(B, 6, d)
+    assert rel_l2(host(e), re) <= 1e-4
+    assert rel_l2(host(e0), re0) <= 1e-4
+    one, one0, t1 = torch.empty_like(e[:1]), torch.empty_like(e0[:1]), torch.empty(4, device="cuda")
+    for b in range(B):
+        t1[:1] = td[b]
+        w.wam_time_embed_fwd(m, t1[:1], one, one0, ws)
+        assert torch.equal(one[0], e[b]) and torch.equal(one0[0], e0[b]), b
 
 
 def test_text_projection():
