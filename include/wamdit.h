@@ -465,8 +465,9 @@ typedef struct {
  * are rewritten by every computed step, as by a single step.  The text conditions every
  * step alike, so when io->ctx_kv is NULL the loop projects the text and each block's
  * cross-attention K|V once, before the first step, into its workspace (n_layers * B *
- * Lc * 2d bf16 more) and every step reads them; results are those of independent
- * steps.  DiT caching is decided on the device: after each computed step the cosine
+ * Lc * 2d bf16 more) and every step reads them; likewise the schedule's time embeddings
+ * and folded modulation, for up to 8 / B steps at a time (B * (8 + 4 n_layers) * d fp32 more
+ * per step of such a group); results are, bit for bit, those of independent steps.  DiT caching is decided on the device: after each computed step the cosine
  * similarity of its velocity with the previous computed one is reduced on the GPU, and a
  * reused step's kernels read that decision from the workspace and return at entry.  The
  * loop never synchronizes or allocates, so a caller can capture a whole call in a graph

@@ -708,6 +708,7 @@ wam_status check_model_common(const wam_model& m) {
   return WAM_OK;
 }
 
+// (the figure the header states; the hidden layer alone is kept there)
 size_t time_ws(const wam_dims& D, int32_t B) { return align256((size_t)B * (D.freq_dim + D.d) * 4); }
 
 wam_status time_run(const wam_model& m, int32_t B, const float* t, float* e, float* e0, char* ws, hipStream_t s) {
@@ -807,7 +808,7 @@ wam_status head_run(const wam_model& m, int32_t B, int32_t F, int32_t Hl, int32_
 
 // Every block's cross-attention K|V of the projected text ctx (B*Lc rows, the same input
 // for every block) into kv + l*kv_layer for the first n blocks, in grouped launches of up
-// to WAM_GEMM_GROUP_MAX blocks: the tiles and arithmetic of one launch per block, but the
+// to WAM_GEMM_GROUP_MAX blocks: bit for bit the products of one launch per block, but the
 // 512-row products fill the chip together instead of ~1.25 rounds each.  Blocks with bf16
 // weights and blocks with FP8 weights form separate groups; for the FP8 ones the text is
 // quantized once (per-row scales, as for any FP8 projection) and shared.
@@ -1207,7 +1208,7 @@ DenoiseWs denoise_ws(const wam_model& m, const wam_step_io& io, const wam_denois
   w.trow = off; off += 256;
   w.te = off; off += align256(rows * d * 4);
   w.te0 = off; off += align256(rows * 6 * d * 4);
-  w.thid = off; off += time_ws(m.dims, (int32_t)rows);
+  w.thid = off; off += align256(rows * d * 4);
   w.tpq = off; off += align256((size_t)std::max(m.dims.n_layers, 0) * 2 * rows * 2 * d * 4);
   w.total = off;
   return w;

@@ -487,7 +487,7 @@ constexpr int GEMV_LDS = 16384;
 
 template <int B, int WR, bool SIN>
 __global__ __launch_bounds__(256, 2) void gemv_kernel(int N, int K, int kc, const float* __restrict__ x,
-                                                   int act, const bf16* __restrict__ W,
+                                                   const bf16* __restrict__ W,
                                                    const float* __restrict__ bias, float* __restrict__ out,
                                                    const int32_t* skip) {
   extern __shared__ __attribute__((aligned(16))) float xs[];  // B * kc floats
@@ -540,9 +540,8 @@ __global__ __launch_bounds__(256, 2) void gemv_kernel(int N, int K, int kc, cons
           if (i < n4) {
             const int b = i / kn4, k = (i - b * kn4) * 4;
             f32x4 u = v[j];
-            if (act == GEMV_ACT_SILU)
 #pragma unroll
-              for (int e = 0; e < 4; ++e) u[e] = silu_f(u[e]);
+            for (int e = 0; e < 4; ++e) u[e] = silu_f(u[e]);
             *reinterpret_cast<f32x4*>(xs + b * kn + k) = u;
           }
         }
@@ -685,7 +684,7 @@ hipError_t launch_rope_qkv(const RopeArgs& a, hipStream_t s) {
 
 namespace {
 template <int WR, bool SIN>
-hipError_t launch_gemv_rows(int32_t B, int32_t N, int32_t K, const float* x, int32_t act, const bf16* w,
+hipError_t launch_gemv_rows(int32_t B, int32_t N, int32_t K, const float* x, const bf16* w,
                             const float* bias, float* out, hipStream_t s, const int32_t* skip) {
   // columns per pass: all of K when B x K floats fit, else a multiple of 512 (B <= 8: at
   // least 2048); the LDS is sized to the pass, so small inputs leave room for more
@@ -694,14 +693,14 @@ hipError_t launch_gemv_rows(int32_t B, int32_t N, int32_t K, const float* x, int
   const dim3 grid((N + 4 * WR - 1) / (4 * WR)), block(256);
   const size_t lds = (size_t)B * kc * sizeof(float);
   switch (B) {
-    case 1: hipLaunchKernelGGL((gemv_kernel<1, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
-    case 2: hipLaunchKernelGGL((gemv_kernel<2, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
-    case 3: hipLaunchKernelGGL((gemv_kernel<3, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
-    case 4: hipLaunchKernelGGL((gemv_kernel<4, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
-    case 5: hipLaunchKernelGGL((gemv_kernel<5, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
-    case 6: hipLaunchKernelGGL((gemv_kernel<6, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
-    case 7: hipLaunchKernelGGL((gemv_kernel<7, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
-    default: hipLaunchKernelGGL((gemv_kernel<8, WR, SIN>), grid, block, lds, s, N, K, kc, x, act, w, bias, out, skip); break;
+    case 1: hipLaunchKernelGGL((gemv_kernel<1, WR, SIN>), grid, block, lds, s, N, K, kc, x, w, bias, out, skip); break;
+    case 2: hipLaunchKernelGGL((gemv_kernel<2, WR, SIN>), grid, block, lds, s, N, K, kc, x, w, bias, out, skip); break;
+    case 3: hipLaunchKernelGGL((gemv_kernel<3, WR, SIN>), grid, block, lds, s, N, K, kc, x, w, bias, out, skip); break;
+    case 4: hipLaunchKernelGGL((gemv_kernel<4, WR, SIN>), grid, block, lds, s, N, K, kc, x, w, bias, out, skip); break;
+    case 5: hipLaunchKernelGGL((gemv_kernel<5, WR, SIN>), grid, block, lds, s, N, K, kc, x, w, bias, out, skip); break;
+    case 6: hipLaunchKernelGGL((gemv_kernel<6, WR, SIN>), grid, block, lds, s, N, K, kc, x, w, bias, out, skip); break;
+    case 7: hipLaunchKernelGGL((gemv_kernel<7, WR, SIN>), grid, block, lds, s, N, K, kc, x, w, bias, out, skip); break;
+    default: hipLaunchKernelGGL((gemv_kernel<8, WR, SIN>), grid, block, lds, s, N, K, kc, x, w, bias, out, skip); break;
   }
   return hipGetLastError();
 }
@@ -712,12 +711,12 @@ hipError_t launch_gemv(int32_t B, int32_t N, int32_t K, const float* x, int32_t 
   if (B <= 0 || N <= 0) return hipSuccess;
   if (B > GEMV_MAXB || K % 8 != 0) return hipErrorInvalidValue;
   const bf16* w = static_cast<const bf16*>(W);
-  if (act == GEMV_ACT_SINUSOID) return launch_gemv_rows<2, true>(B, N, K, x, act, w, bias, out, s, skip);
+  if (act == GEMV_ACT_SINUSOID) return launch_gemv_rows<2, true>(B, N, K, x, w, bias, out, s, skip);
   // two rows per wavefront: up to 24 features per CU for one sample (5120 x 5120 11.9 us against
   // 14.4 with four, 9216 x 1536 11.6 against 8.7), up to 12 for several (at B = 8 3072 x 512 8.6
   // against 10.2, 5120 x 5120 76.8 against 49.5)
-  if (N <= (B == 1 ? 24 : 12) * cu_count()) return launch_gemv_rows<2, false>(B, N, K, x, act, w, bias, out, s, skip);
-  return launch_gemv_rows<4, false>(B, N, K, x, act, w, bias, out, s, skip);
+  if (N <= (B == 1 ? 24 : 12) * cu_count()) return launch_gemv_rows<2, false>(B, N, K, x, w, bias, out, s, skip);
+  return launch_gemv_rows<4, false>(B, N, K, x, w, bias, out, s, skip);
 }
 
 hipError_t launch_patchify(int32_t B, int32_t C, int32_t F, int32_t Hl, int32_t Wl, const void* z,

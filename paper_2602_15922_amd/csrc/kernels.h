@@ -169,7 +169,7 @@ hipError_t launch_quant_scaled(int64_t n, const void* x, float inv, void* q, hip
 
 // out[b][n] = act(x[b][:]) . W[n][:] + bias[n]  (fp32 in/out, bf16 W [N][K])
 // GEMV_ACT_SINUSOID: the input is the K-wide sinusoid of 1000 * x[b] (x [B]) instead.
-enum { GEMV_ACT_NONE = 0, GEMV_ACT_SILU = 1, GEMV_ACT_SINUSOID = 2 };
+enum { GEMV_ACT_SILU, GEMV_ACT_SINUSOID };
 hipError_t launch_gemv(int32_t B, int32_t N, int32_t K, const float* x, int32_t act, const void* W,
                        const float* bias, float* out, hipStream_t s, const int32_t* skip = nullptr);
 // latent [B][C][F][Hl][Wl] bf16 -> tokens [B][F*Hg*Wg][C*4] bf16
